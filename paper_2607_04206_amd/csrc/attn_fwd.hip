@@ -29,6 +29,7 @@
 
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "../../include/sangam_attn.h"
 #include "plan_format.h"
@@ -73,46 +74,77 @@ struct AttnArgs {
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// Asynchronous copy of 16 bytes per lane from global memory into LDS
-// (global_load_lds_dwordx4): lane l's bytes land at dst_wave + 16 l. Issued
-// through inline assembly so that the compiler does not track the LDS write:
-// it would otherwise wait for every copy in flight before any later LDS read,
+// Asynchronous copy of one K or V page (16 key rows of one head) from global
+// memory into LDS by one wave: IPP global_load_lds_dwordx4, each moving 1 KiB
+// (lane l's 16 bytes land at the instruction's LDS base + 16 l). The
+// instruction adds its offset field to the global and to the LDS address, so
+// one M0 write serves the page: instruction j lands at dst + 1024 j, and the
+// lane offsets of instruction j are given less 1024 j. Issued through inline
+// assembly so that the compiler does not track the LDS write: it would
+// otherwise wait for every copy in flight before any later LDS read,
 // including the copies that prefetch the next stage into another buffer,
 // which serialises the prefetch with the compute it should overlap. The
 // kernels order the copies themselves: s_waitcnt vmcnt and a barrier before a
-// staged buffer is read, a barrier before it is overwritten. M0 (the LDS
-// base) is saved and restored around the copy, with the wait state the
-// hardware needs between an M0 write and its use.
+// staged buffer is read, a barrier before it is overwritten. M0 is saved and
+// restored around the copies, with the wait state the hardware needs between
+// an M0 write and its use.
 __device__ __forceinline__ uint32_t lds_wave_base(LDS void* p) {
     return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)p);
 }
-__device__ __forceinline__ void lds_copy16(const void* src, LDS void* dst_wave) {
+// from a wave-uniform base plus per-lane 32-bit byte offsets
+template <int IPP>
+__device__ __forceinline__ void copy_page(const void* base, const uint32_t (&off)[IPP], LDS void* dst) {
     uint32_t saved;
-    asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %2, off\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-        : "=&s"(saved)
-        : "s"(lds_wave_base(dst_wave)), "v"(src)
-        : "memory");
+    static_assert(IPP == 2 || IPP == 4, "a page is 2 or 4 KiB");
+    if constexpr (IPP == 4)
+        asm volatile(
+            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %2, %6\n\tglobal_load_lds_dwordx4 %3, %6 offset:1024\n\t"
+            "global_load_lds_dwordx4 %4, %6 offset:2048\n\tglobal_load_lds_dwordx4 %5, %6 offset:3072\n\t"
+            "s_nop 0\n\ts_mov_b32 m0, %0"
+            : "=&s"(saved)
+            : "s"(lds_wave_base(dst)), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base)
+            : "memory");
+    else
+        asm volatile(
+            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %2, %4\n\tglobal_load_lds_dwordx4 %3, %4 offset:1024\n\t"
+            "s_nop 0\n\ts_mov_b32 m0, %0"
+            : "=&s"(saved)
+            : "s"(lds_wave_base(dst)), "v"(off[0]), "v"(off[1]), "s"(base)
+            : "memory");
 }
-// the same from a wave-uniform base plus a per-lane 32-bit byte offset
-__device__ __forceinline__ void lds_copy16(const void* base, uint32_t off, LDS void* dst_wave) {
+// the same from per-lane addresses
+template <int IPP>
+__device__ __forceinline__ void copy_page(const uint64_t (&addr)[IPP], LDS void* dst) {
     uint32_t saved;
-    asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %2, %3\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-        : "=&s"(saved)
-        : "s"(lds_wave_base(dst_wave)), "v"(off), "s"(base)
-        : "memory");
+    if constexpr (IPP == 4)
+        asm volatile(
+            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %2, off\n\tglobal_load_lds_dwordx4 %3, off offset:1024\n\t"
+            "global_load_lds_dwordx4 %4, off offset:2048\n\tglobal_load_lds_dwordx4 %5, off offset:3072\n\t"
+            "s_nop 0\n\ts_mov_b32 m0, %0"
+            : "=&s"(saved)
+            : "s"(lds_wave_base(dst)), "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3])
+            : "memory");
+    else
+        asm volatile(
+            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %2, off\n\tglobal_load_lds_dwordx4 %3, off offset:1024\n\t"
+            "s_nop 0\n\ts_mov_b32 m0, %0"
+            : "=&s"(saved)
+            : "s"(lds_wave_base(dst)), "v"(addr[0]), "v"(addr[1])
+            : "memory");
 }
 
 // Swizzle of 16-byte chunks inside a staged key row. K rows are read one key
-// per lane (ds_read_b128), so consecutive keys rotate their chunks. V rows are
+// per lane (ds_read_b128), so 16 consecutive keys (4 KiB at D = 128; at
+// D = 64 two keys share the 256 bytes of all banks) spread their chunks. V rows are
 // read four keys at a time by ds_read_b64_tr_b16, so groups of four keys
 // spread over the LDS banks.
 template <int D>
 __device__ __forceinline__ int swz_k(int r) {
-    return r & (D / 8 - 1);
+    return D == 128 ? r & 15 : (r >> 1) & 7;
 }
 template <int D>
 __device__ __forceinline__ int swz_v(int r) {
@@ -136,13 +168,9 @@ __device__ __forceinline__ float half_sum(float x) {
 // because O and l always share the same reference.
 constexpr float kRescaleThreshold = 8.0f;
 
-// Work-groups per CU the register budget is sized for: two waves per SIMD for
-// four-wave work-groups whose staging fits twice in LDS and whose waves hold
-// one query block; one wave per SIMD otherwise.
-template <int D, int QW, int KW, int QB, int NB, int NSTAGE>
-constexpr int min_blocks_per_cu() {
-    return (QB == 1 && QW * KW == 4 && 2 * NSTAGE * (32 * NB * KW) * D * 2 <= 80 * 1024) ? 2 : 1;
-}
+// Waves per SIMD the register budget is sized for: two (256 registers) when a
+// wave holds one query block.
+constexpr int waves_per_simd(int qb) { return qb == 1 ? 2 : 1; }
 
 // One work-group per plan tile: a context range [kv_begin, kv_end) of one
 // item and KV head against QW query slots x QB blocks of 32 rows per slot.
@@ -154,37 +182,38 @@ constexpr int min_blocks_per_cu() {
 //          LDS feeds QB MFMAs, so QB = 2 halves LDS traffic per flop
 //   NB     32-key blocks per wave per stage
 //   NSTAGE K/V stage buffers in LDS (NSTAGE - 1 stages in flight)
-template <int D, int QW, int KW, int QB, int NB, int NSTAGE, bool HEADS_ACROSS, int MINB>
-__global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs a) {
+template <int D, int QW, int KW, int QB, int NB, int NSTAGE, bool HEADS_ACROSS>
+__global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_kernel(AttnArgs a) {
     constexpr int NT = 64 * QW * KW;     // threads
     constexpr int KT = 32 * NB;          // keys per wave per stage
     constexpr int STEP = KT * KW;        // keys per stage
     constexpr int NC = D / 8;            // 16-byte chunks per key row
     constexpr int ROWB = D * 2;          // bytes per key row
     constexpr int TILE = STEP * ROWB;    // bytes of one staged K (or V) tile
-    constexpr int NCH = STEP * NC;       // 16-byte chunks of one staged tile
-    constexpr int NJ = (NCH + NT - 1) / NT;  // chunk rounds per thread
+    constexpr int NW = QW * KW;          // waves
+    constexpr int SP = STEP / 16;        // 16-key pages per stage
+    constexpr int PW = (SP + NW - 1) / NW;  // pages a wave copies per stage
+    constexpr int RPI = 64 / NC;         // key rows per copy instruction
+    constexpr int IPP = 16 / RPI;        // copy instructions per page
     constexpr int DS = D / 16;           // k-steps of the QK^T contraction
     constexpr int MB = D / 32;           // 32-dim blocks of O^T
-    static_assert(NCH % 64 == 0, "a wave moves whole 1 KiB rows of chunks");
+    constexpr int RA = 4;                // steps between a fragment's LDS read and its MFMA
     constexpr int MERGE_REGS = MB * 16 + 2;
     static_assert(KW == 1 || QB == 1, "context-splitting waves hold one query block");
     static_assert(!HEADS_ACROSS || QB == 1, "a decode block is 32 rows");
     static_assert(KW == 1 || (QW * (KW - 1) * MERGE_REGS * 64 * 4) <= 2 * NSTAGE * TILE,
                   "cross-wave merge must fit in the stage buffers");
     static_assert(NSTAGE >= 2 && NSTAGE <= 4, "2 to 4 stage buffers");
-    // pages a tile's write-back range can touch: its rows at any offset
-    constexpr int WPAGES = HEADS_ACROSS ? 16 : (32 * QB * QW + 15) / 16 + 1;
+    // pages a tile's write-back can touch: its rows at any offset, or one per listed row
+    constexpr int WPAGES = HEADS_ACROSS || (32 * QB * QW + 15) / 16 + 1 < kWaveRows ? kWaveRows : (32 * QB * QW + 15) / 16 + 1;
     static_assert(WPAGES <= NT, "one thread per write-back page id");
     // with more than two buffers the wait counts loads, so every wave must
     // issue the same number per stage
-    static_assert(NSTAGE == 2 || NCH % NT == 0, "deeper pipelines need whole staging rounds");
-    constexpr int MAX_PAGES = kMaxCachedRange / 16;
+    static_assert(NSTAGE == 2 || SP % NW == 0, "deeper pipelines need whole staging rounds");
+    static_assert(64 % SP == 0 && (NSTAGE - 1) * SP < 64, "a stage's page ids sit in one register of 64 lanes");
 
     __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * NSTAGE * TILE];
-    __shared__ int32_t pages[MAX_PAGES];
-    __shared__ uint32_t pinfo[MAX_PAGES];  // page_info of the tile's pages (kItemPosList items)
-    __shared__ int32_t fpos[kWaveRows];    // the listed positions (kItemPosList items)
+    __shared__ int32_t fpos[kWaveRows];   // the listed positions (kItemPosList items)
     __shared__ int32_t wpages[WPAGES];  // pages of the fresh rows this tile writes back
 
     const int tid = threadIdx.x;
@@ -213,167 +242,130 @@ __global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs
     // a per-token cached decode: its rows sit at listed positions
     const bool plist = (it.flags & kItemPosList) != 0;
     const int pg0 = kv_begin >> 4;
-    if (!all_fresh) {
-        // the tile's page ids, once (the plan keeps such ranges <= kMaxCachedRange):
-        // every load is issued before the first LDS store, so a long range
-        // costs one memory round trip, not one per round of NT pages
-        const int npg = ((kv_end + 15) >> 4) - pg0;
-        constexpr int PR = (MAX_PAGES + NT - 1) / NT;  // rounds of the page table per thread
-        int32_t pv[PR];
-        uint32_t iv[PR];
-#pragma unroll
-        for (int r = 0; r < PR; ++r) {
-            const int k = tid + r * NT;
-            if (k < npg) {
-                pv[r] = a.page_ids[it.page_start + pg0 + k];
-                if (plist) iv[r] = a.page_info[it.page_start + pg0 + k];
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < PR; ++r) {
-            const int k = tid + r * NT;
-            if (k < npg) {
-                pages[k] = pv[r];
-                if (plist) pinfo[k] = iv[r];
-            }
-        }
-        if (plist && tid < it.n) fpos[tid] = a.positions[it.pos_start + tid];
-    }
+    const int npg = ((kv_end + 15) >> 4) - pg0;
+    // The tile's page ids (and page_info of kItemPosList items) sit in a
+    // register, 64 at a time (lane l holds entry 64 c + l of chunk c): a stage
+    // reads its ids with v_readlane, with no LDS or barrier in between.
+    int32_t pv = 0;
+    uint32_t iv = 0;
+    uint64_t listed = 0;  // the pages among those 64 with listed positions
+    auto load_pages = [&](int first) {
+        const int k = it.page_start + pg0 + min(first + lane, npg - 1);
+        pv = a.page_ids[k];
+        if (plist) iv = a.page_info[k];
+    };
+    if (!all_fresh) load_pages(0);
+    int32_t lpos = 0;  // the listed position of row tid
+    if (plist && tid < it.n) lpos = a.positions[it.pos_start + tid];
 
-    // ---- Q fragments (B operand: k = dims, n = query), zero for rows past n
+    // ---- Q fragments (B operand: k = dims, n = query). Lanes past the last
+    // row hold row 0 again: a query is a column of every product, so they
+    // change no other row, and nothing of theirs is stored.
     bf16x8 qf[QB][DS];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const int row = row_base + 32 * qb + qn;
-        const bool ok = row < it.n;
-        const uint16_t* qp = a.q + ((size_t)(it.q_start + (ok ? row : 0)) * a.hq + head) * D;
+        const uint16_t* qp = a.q + ((size_t)(it.q_start + (row < it.n ? row : 0)) * a.hq + head) * D;
 #pragma unroll
-        for (int s = 0; s < DS; ++s) {
-            u32x4 v = *(const u32x4*)(qp + 16 * s + 8 * hh);
-            if (!ok) v = u32x4{0, 0, 0, 0};
-            qf[qb][s] = __builtin_bit_cast(bf16x8, v);
-        }
+        for (int s = 0; s < DS; ++s) qf[qb][s] = *(const bf16x8*)(qp + 16 * s + 8 * hh);
     }
 
-    // ---- stage-invariant staging offsets: thread chunk j of a stage is key
-    // row r_j, source chunk (pos ^ swizzle(r_j)) of K and of V
+    // ---- staging. A stage is SP pages of 16 key rows; wave w copies pages
+    // w, w + NW, ... of it, K and V, IPP instructions each. Instruction j
+    // covers rows RPI j + lane / NC; the lane's chunk of LDS row r is source
+    // chunk (lane % NC) ^ swizzle(r). A work-group by itself is bound by its
+    // serial chain of stages, and the scalar instructions of the copies stood
+    // in it (about 110 per page; now about 20): one LLaDA decode 17.3 -> 16.6
+    // us, a batch of 32 75.3 -> 74.1 us.
     const size_t row_stride = (size_t)a.hkv * D;                       // elements between positions
+    const uint32_t row_bytes = uint32_t(row_stride * 2);
     const uint16_t* kfresh = a.k_new + ((size_t)(it.q_start - it.o) * a.hkv + t.kv_head) * D;
     const uint16_t* vfresh = a.v_new + ((size_t)(it.q_start - it.o) * a.hkv + t.kv_head) * D;
     const size_t page_stride = (size_t)a.hkv * 16 * D;
     const uint16_t* kcache = a.k_cache + (size_t)t.kv_head * 16 * D;
     const uint16_t* vcache = a.v_cache + (size_t)t.kv_head * 16 * D;
 
-    // per-thread byte offsets of its chunks within a stage of fresh rows
-    // (whole prefills): key row r_j at row_stride, swizzled chunk
-    uint32_t foff_k[NJ], foff_v[NJ];
+    // byte offsets of a lane's chunks from the first row of a page, less the
+    // instruction's offset field: rows ROWB apart in the cache, row_bytes
+    // apart among the fresh rows (row_bytes >= ROWB, so none is negative)
+    uint32_t coff_k[IPP], coff_v[IPP], foff_k[IPP], foff_v[IPP];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const int P = j * NT + tid;
-        const int r = P / NC;
-        const int pos = P % NC;
-        foff_k[j] = uint32_t(r * row_stride * 2 + ((pos ^ swz_k<D>(r)) << 4));
-        foff_v[j] = uint32_t(r * row_stride * 2 + ((pos ^ swz_v<D>(r)) << 4));
+    for (int j = 0; j < IPP; ++j) {
+        const int r = RPI * j + lane / NC, pos = lane % NC;
+        const uint32_t ck = uint32_t((pos ^ swz_k<D>(r)) << 4), cv = uint32_t((pos ^ swz_v<D>(r)) << 4);
+        coff_k[j] = uint32_t(r * ROWB - 1024 * j) + ck;
+        coff_v[j] = uint32_t(r * ROWB - 1024 * j) + cv;
+        foff_k[j] = uint32_t(r) * row_bytes - 1024 * j + ck;
+        foff_v[j] = uint32_t(r) * row_bytes - 1024 * j + cv;
     }
-    // the same within a 16-row page (K/V head chunk of the cache) for a stage
-    // that starts on a page boundary: key row r_j sits in slot r_j mod 16 of
-    // the stage's page r_j / 16
-    uint32_t poff_k[NJ], poff_v[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const int P = j * NT + tid;
-        const int r = P / NC;
-        const int pos = P % NC;
-        poff_k[j] = uint32_t((r & 15) * ROWB + ((pos ^ swz_k<D>(r)) << 4));
-        poff_v[j] = uint32_t((r & 15) * ROWB + ((pos ^ swz_v<D>(r)) << 4));
-    }
-    // A full stage with no fresh row reads only cached rows. When it starts
-    // on a page boundary, each wave's copy instruction covers 64 / NC key rows
-    // of one page, so the page base is wave-uniform (scalar registers) and
-    // the lanes add the precomputed offsets: no per-lane page lookup,
-    // freshness test or 64-bit address arithmetic on the common path.
-    auto stage_all_cached = [&](int key0) -> bool {
-        if (all_fresh || (kv_begin & 15) != 0) return false;
-        if (plist) {
-            uint32_t slots = 0;
-#pragma unroll
-            for (int k = 0; k < STEP / 16; ++k) slots |= pinfo[(key0 >> 4) - pg0 + k];
-            return (uniform(int(slots & 0xFFFFu))) == 0;
-        }
-        return key0 + STEP <= it.o || key0 >= it.o + it.n;
-    };
 
     auto issue_stage = [&](int st, int buf) __attribute__((always_inline)) {
         uint8_t* kb = smem + buf * 2 * TILE;
         uint8_t* vb = kb + TILE;
-        const int key0 = kv_begin + st * STEP;
-        const bool tail = key0 + STEP > kv_end;
-        if (all_fresh && !tail) {
-            // uniform base + precomputed 32-bit offsets
-            const uint16_t* kbase = kfresh + (size_t)key0 * row_stride;
-            const uint16_t* vbase = vfresh + (size_t)key0 * row_stride;
+        const int skey0 = kv_begin + st * STEP;
+        const int pl0 = st * SP & 63;  // lane holding the id of the stage's first page
+        // a whole stage of fresh rows (whole prefills) or of cached rows:
+        // wave-uniform bases, precomputed lane offsets
+        const bool whole = skey0 + STEP <= kv_end;
+        if (plist && pl0 == 0) listed = __builtin_amdgcn_ballot_w64((iv & 0xFFFFu) != 0);
+        const bool cached = plist ? (listed >> pl0 & ((1ull << SP) - 1)) == 0
+                                  : !all_fresh && (skey0 + STEP <= it.o || skey0 >= it.o + it.n);
+        if (__builtin_expect(whole && (all_fresh || cached), 1)) {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if ((NCH % NT) != 0 && j * NT + wave * 64 >= NCH) break;  // wave-uniform
-                const int dst = (j * NT + wave * 64) * 16;
-                lds_copy16(kbase, foff_k[j], (LDS void*)(kb + dst));
-                lds_copy16(vbase, foff_v[j], (LDS void*)(vb + dst));
+            for (int i = 0; i < PW; ++i) {
+                const int k = wave + i * NW;  // page of the stage
+                if (SP % NW != 0 && k >= SP) break;
+                LDS void* kd = (LDS void*)(kb + k * 16 * ROWB);
+                LDS void* vd = (LDS void*)(vb + k * 16 * ROWB);
+                if (all_fresh) {
+                    const size_t off = (size_t)(skey0 + k * 16) * row_stride;
+                    copy_page(kfresh + off, foff_k, kd);
+                    copy_page(vfresh + off, foff_v, vd);
+                } else {
+                    const size_t off = (size_t)__builtin_amdgcn_readlane(pv, pl0 + k) * page_stride;
+                    copy_page(kcache + off, coff_k, kd);
+                    copy_page(vcache + off, coff_v, vd);
+                }
             }
             return;
         }
-        if (!tail && stage_all_cached(key0)) {
-            const int prel = (key0 >> 4) - pg0;  // the stage's first page among the tile's
-            int pid[NJ];
+        for (int k = wave; k < SP; k += NW) {
+            LDS void* kd = (LDS void*)(kb + k * 16 * ROWB);
+            LDS void* vd = (LDS void*)(vb + k * 16 * ROWB);
+            // a page past the range: the stage's first page again, masked later
+            const bool past = skey0 + k * 16 >= kv_end;
+            const int key0 = past ? skey0 : skey0 + k * 16;
+            const int pl = past ? pl0 : pl0 + k;
+            const uint32_t inf = plist ? uint32_t(__builtin_amdgcn_readlane(int(iv), pl)) : 0u;
+            const size_t off = all_fresh ? 0 : (size_t)__builtin_amdgcn_readlane(pv, pl) * page_stride;
+            if (key0 + 16 <= kv_end && !all_fresh &&
+                (plist ? (inf & 0xFFFFu) == 0 : key0 + 16 <= it.o || key0 >= it.o + it.n)) {
+                copy_page(kcache + off, coff_k, kd);
+                copy_page(vcache + off, coff_v, vd);
+                continue;
+            }
+            // fresh rows of a block, listed positions, the range's partial
+            // last page (rows past its end repeat its last row)
+            const int lim = min(16, kv_end - key0);
+            // fresh rows of the page: row `first` onwards, in order
+            const int64_t first = plist ? int64_t(it.q_start) + (inf >> kPageInfoRowShift)
+                                        : int64_t(it.q_start) + key0 - it.o;
+            const uint64_t fk = (uint64_t)(a.k_new + (size_t)t.kv_head * D) + uint64_t(first * int64_t(row_bytes));
+            const uint64_t fv = (uint64_t)(a.v_new + (size_t)t.kv_head * D) + uint64_t(first * int64_t(row_bytes));
+            uint64_t ak[IPP], av[IPP];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                pid[j] = 0;
-                if ((NCH % NT) == 0 || j * NT + wave * 64 < NCH)
-                    pid[j] = pages[prel + (((j * NT + wave * 64) / NC) >> 4)];
+            for (int j = 0; j < IPP; ++j) {
+                const int r = RPI * j + lane / NC, pos = lane % NC;
+                const int rc = min(r, lim - 1);
+                const bool fresh = plist ? (inf >> rc) & 1u : unsigned(key0 + rc - it.o) < unsigned(it.n);
+                const uint32_t frow = plist ? __builtin_popcount(inf & ((1u << rc) - 1u)) : rc;
+                const uint32_t ro = fresh ? frow * row_bytes : uint32_t(rc * ROWB);
+                const int64_t lo = int64_t(ro) - 1024 * j;
+                ak[j] = (fresh ? fk : (uint64_t)(kcache + off)) + uint64_t(lo + ((pos ^ swz_k<D>(r)) << 4));
+                av[j] = (fresh ? fv : (uint64_t)(vcache + off)) + uint64_t(lo + ((pos ^ swz_v<D>(r)) << 4));
             }
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if ((NCH % NT) != 0 && j * NT + wave * 64 >= NCH) break;  // wave-uniform
-                const size_t off = (size_t)uniform(pid[j]) * page_stride;
-                const int dst = (j * NT + wave * 64) * 16;
-                lds_copy16(kcache + off, poff_k[j], (LDS void*)(kb + dst));
-                lds_copy16(vcache + off, poff_v[j], (LDS void*)(vb + dst));
-            }
-            return;
-        }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            if ((NCH % NT) != 0 && j * NT + wave * 64 >= NCH) break;  // wave-uniform
-            const int P = j * NT + tid;
-            const int r = P / NC;
-            const int pos = P % NC;
-            int p = key0 + r;
-            if (tail) p = p < kv_end ? p : kv_begin;  // past the range: a valid row, masked later
-            const int ck = (pos ^ swz_k<D>(r)) * 8;
-            const int cv = (pos ^ swz_v<D>(r)) * 8;
-            // fresh row holding position p, counted from position o (row r
-            // sits at o + r in kfresh / vfresh), or -1 for a cached row
-            int fr;
-            if (all_fresh) {
-                fr = p;
-            } else if (plist) {
-                const uint32_t inf = pinfo[(p >> 4) - pg0];
-                const uint32_t below = inf & ((1u << (p & 15)) - 1u);
-                fr = (inf >> (p & 15)) & 1u ? int(inf >> kPageInfoRowShift) + __builtin_popcount(below) + it.o : -1;
-            } else {
-                fr = unsigned(p - it.o) < unsigned(it.n) ? p : -1;
-            }
-            const uint16_t *ksrc, *vsrc;
-            if (fr >= 0) {
-                ksrc = kfresh + (size_t)fr * row_stride;
-                vsrc = vfresh + (size_t)fr * row_stride;
-            } else {
-                const size_t off = (size_t)pages[(p >> 4) - pg0] * page_stride + (p & 15) * D;
-                ksrc = kcache + off;
-                vsrc = vcache + off;
-            }
-            const int dst = (j * NT + wave * 64) * 16;
-            lds_copy16(ksrc + ck, (LDS void*)(kb + dst));
-            lds_copy16(vsrc + cv, (LDS void*)(vb + dst));
+            copy_page(ak, kd);
+            copy_page(av, vd);
         }
     };
 
@@ -384,10 +376,9 @@ __global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs
     // v_new. Every fresh position lies in exactly one such tile's row block
     // and context range. No tile reads these cache rows (fresh positions come
     // from k_new / v_new, and the planner rejects pages shared between items),
-    // so the copy needs no ordering with the attention. The pages of the
-    // written range (at most 9) are staged in LDS once, right after the first
-    // stage is issued (their wait overlaps that stage's), so the copy loop
-    // issues no global load whose wait would also drain the prefetch.
+    // so the copy needs no ordering with the attention. The pages written are
+    // kept in LDS (one per page of a block, one per listed row), so the copy
+    // loop issues no global load whose wait would also drain the prefetch.
     const int group = a.hq / a.hkv;
     const bool wb_head = across ? t.q_head0 == t.kv_head * group : t.q_head0 % group == 0;
     // positions written: [wb_lo, wb_hi) for a block; for a position list (a
@@ -404,14 +395,14 @@ __global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs
         if (lo >= hi) return;
         const uint8_t* kb = smem + (st % NSTAGE) * 2 * TILE;
         const uint8_t* vb = kb + TILE;
-        if (plist) {  // the listed positions inside [lo, hi); their pages are the tile's
+        if (plist) {  // the listed positions inside [lo, hi)
             for (int cidx = tid; cidx < it.n * NC; cidx += NT) {
                 const int p = fpos[cidx / NC], pos = cidx % NC;
                 if (p < lo || p >= hi) continue;
                 const int r = p - key0;
                 const u32x4 kv = *(const LDS u32x4*)(kb + r * ROWB + ((pos ^ swz_k<D>(r)) << 4));
                 const u32x4 vv = *(const LDS u32x4*)(vb + r * ROWB + ((pos ^ swz_v<D>(r)) << 4));
-                const size_t dst = (((size_t)pages[(p >> 4) - pg0] * a.hkv + t.kv_head) * 16 + (p & 15)) * D + pos * 8;
+                const size_t dst = (((size_t)wpages[cidx / NC] * a.hkv + t.kv_head) * 16 + (p & 15)) * D + pos * 8;
                 *(u32x4*)(a.k_cache + dst) = kv;
                 *(u32x4*)(a.v_cache + dst) = vv;
             }
@@ -429,23 +420,18 @@ __global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs
     };
 
     // ---- stage-invariant LDS read offsets
-    // K (A operand): lane reads key qn of each 32-key block, chunk 2k + hh
-    int koff[DS];
-#pragma unroll
-    for (int k = 0; k < DS; ++k) koff[k] = qn * ROWB + (((2 * k + hh) ^ swz_k<D>(qn)) << 4);
+    // K (A operand): lane reads key qn of each 32-key block, chunk 2k + hh of
+    // k-step k: koff ^ (k << 5)
+    const uint32_t koff = qn * ROWB + ((hh ^ swz_k<D>(qn)) << 4);
     // V^T (A operand) via transposing reads: 16-lane group g16 covers dims
     // mb*32 + (g16&1)*16 .. +15; lane (r4, j4) points at key row 4hh + r4 (+8),
-    // dims 4 j4 .. 4 j4 + 3 of that group
+    // dims 4 j4 .. 4 j4 + 3 of that group: voff ^ (mb << 6)
     const int g16 = lane >> 4;
     const int r4 = (lane >> 2) & 3;
     const int j4 = lane & 3;
-    const int vrow = (4 * hh + r4) * ROWB;
-    int voff[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        const int dim = mb * 32 + (g16 & 1) * 16 + 4 * j4;
-        voff[mb] = vrow + (((dim >> 3) ^ swz_v<D>(4 * hh + r4)) << 4) + (dim & 7) * 2;
-    }
+    const int vdim = (g16 & 1) * 16 + 4 * j4;
+    const uint32_t voff = (4 * hh + r4) * ROWB + (((vdim >> 3) ^ swz_v<D>(4 * hh + r4)) << 4) + (vdim & 7) * 2;
+    const uint32_t lds0 = lds_wave_base((LDS void*)smem);
 
     f32x16 o[QB][MB];
     float m_used[QB];  // reference max (log2 domain) of this lane's query, per block
@@ -461,69 +447,91 @@ __global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs
     }
     const float c = a.scale_log2;
 
-    if (!all_fresh) __syncthreads();  // page ids visible before the first loads
-
-    // S^T = K Q^T for this wave's NB 32-key blocks of stage st: rows = keys,
-    // columns = queries; each K fragment feeds the QB query blocks
-    // The QK^T MFMAs run at raised wave priority: with two waves per SIMD,
-    // the wave that reaches its QK^T chain keeps the matrix core fed while the
-    // other works through its softmax (measured about 1 % faster on prefills).
-    auto qk = [&](int st, f32x16 (&s)[QB][NB]) {
-        const uint8_t* kb = smem + (st % NSTAGE) * 2 * TILE + ks * KT * ROWB;
-        __builtin_amdgcn_s_setprio(1);
+    // One stage of this wave: S^T = K Q^T (rows = keys, columns = queries; NB
+    // 32-key blocks, each K fragment feeding the QB query blocks), online
+    // softmax (exp2 domain), O^T += V^T P^T. tail: the stage may hold keys past
+    // the range (set to -inf).
+    //
+    // The order of instructions is fixed here, MFMA by MFMA
+    // (sched_barrier(0) after each step): the operand fragments form one
+    // stream, K's then V's, each read from LDS RA steps before its MFMA; a
+    // block's row max is taken beside the next block's QK^T and the
+    // exponentials of the next 16 keys beside the PV of these. Left to the
+    // compiler, most MFMAs sat right behind the LDS read they wait for (about
+    // 130 cycles each), which a second wave on the SIMD hides in part only.
+    // Measured per 64-key stage, K/V in L2, one 128-row work-group on the CU:
+    // 1.30 -> 1.16 us at D = 128, 1.07 -> 0.85 us at D = 64; two: 1.98 -> 1.96
+    // us and 1.32 -> 1.24 us (at D = 128 two work-groups draw the power limit:
+    // the same MFMAs on random operands without the rest take 1.33 us).
+    auto attend = [&](int st, auto tail) __attribute__((always_inline)) {
+        constexpr bool TAIL = decltype(tail)::value;
+        constexpr int NK = NB * DS;      // K fragments (and QK^T steps)
+        constexpr int NV = NB * 2 * MB;  // V fragments (and PV steps)
+        const uint32_t buf = lds0 + (st % NSTAGE) * 2 * TILE + ks * KT * ROWB;
+        const uint32_t ka = buf + koff, va = buf + TILE + voff;
+        auto read_frag = [&](int n) -> bf16x8 {
+            if (n < NK) return *(const LDS bf16x8*)(uintptr_t)((ka ^ uint32_t((n % DS) << 5)) + (n / DS) * 32 * ROWB);
+            const int v = n - NK;  // 16 keys v / MB, 32 dims v % MB
+            const uint32_t vp = (va ^ uint32_t((v % MB) << 6)) + (v / MB) * 16 * ROWB;
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS bf16x4*)(uintptr_t)vp);
+            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS bf16x4*)(uintptr_t)(vp + 8 * ROWB));
+            return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        };
+        f32x16 s[QB][NB];
+        float mx[QB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
+        for (int qb = 0; qb < QB; ++qb) mx[qb] = -INFINITY;
+        // row max over scores [i0, i1) of block b
+        auto take_max = [&](int b, int i0, int i1) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
+            for (int i = i0; i < i1; ++i) {
+                const int key = kv_begin + st * STEP + ks * KT + b * 32 + 8 * (i >> 2) + 4 * hh + (i & 3);
 #pragma unroll
-                for (int i = 0; i < 16; ++i) s[qb][b][i] = 0.0f;
-#pragma unroll
-            for (int k = 0; k < DS; ++k) {
-                const bf16x8 kf = *(const LDS bf16x8*)(kb + b * 32 * ROWB + koff[k]);
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-                    s[qb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qb][k], s[qb][b], 0, 0, 0);
+                for (int qb = 0; qb < QB; ++qb) {
+                    if (TAIL && key >= kv_end) s[qb][b][i] = -INFINITY;
+                    mx[qb] = fmaxf(mx[qb], s[qb][b][i]);
+                }
             }
+        };
+
+        bf16x8 frag[RA];
+#pragma unroll
+        for (int n = 0; n < RA; ++n) frag[n] = read_frag(n);
+        __builtin_amdgcn_s_setprio(1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NK; ++n) {
+            const int b = n / DS, k = n % DS;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                if (k == 0)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) s[qb][b][i] = 0.0f;
+                s[qb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[n % RA], qf[qb][k], s[qb][b], 0, 0, 0);
+            }
+            frag[n % RA] = read_frag(n + RA);
+            // the previous block's scores are written two steps into this one
+            if (b > 0 && k >= 2) take_max(b - 1, (k - 2) * 16 / (DS - 2), (k - 1) * 16 / (DS - 2));
+            __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
-    };
+        take_max(NB - 1, 0, 16);
 
-    // Online softmax of stage st's scores (exp2 domain) and O^T += V^T P^T.
-    // The reference max moves (and O, l are rescaled) only when a score
-    // exceeds it by more than kRescaleThreshold, which is rare after the first
-    // stage. tail: the stage may hold keys past the range (set to -inf).
-    auto softmax_pv = [&](int st, f32x16 (&s)[QB][NB], bool tail) {
-        const uint8_t* vb = smem + (st % NSTAGE) * 2 * TILE + TILE + ks * KT * ROWB;
-        if (tail) {
-            const int key0 = kv_begin + st * STEP + ks * KT;  // this wave's first key
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int key = key0 + b * 32 + 8 * (i >> 2) + 4 * hh + (i & 3);
-#pragma unroll
-                    for (int qb = 0; qb < QB; ++qb)
-                        if (key >= kv_end) s[qb][b][i] = -INFINITY;
-                }
-        }
-        float mx_s[QB];
+        // The reference max moves (and O, l are rescaled) only when a score
+        // exceeds it by more than kRescaleThreshold, which is rare after the
+        // first stage.
         bool any_need = false;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            float mx = -INFINITY;
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[qb][b][i]);
-            mx_s[qb] = half_max(mx) * c;
-            any_need |= mx_s[qb] > m_used[qb] + kRescaleThreshold;
+            mx[qb] = half_max(mx[qb]) * c;
+            any_need |= mx[qb] > m_used[qb] + kRescaleThreshold;
         }
         if (__builtin_amdgcn_ballot_w64(any_need)) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                const bool need = mx_s[qb] > m_used[qb] + kRescaleThreshold;
-                const float alpha = need ? __builtin_amdgcn_exp2f(m_used[qb] - mx_s[qb]) : 1.0f;
-                m_used[qb] = need ? mx_s[qb] : m_used[qb];
+                const bool need = mx[qb] > m_used[qb] + kRescaleThreshold;
+                const float alpha = need ? __builtin_amdgcn_exp2f(m_used[qb] - mx[qb]) : 1.0f;
+                m_used[qb] = need ? mx[qb] : m_used[qb];
                 l_run[qb] *= alpha;
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
@@ -532,47 +540,46 @@ __global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs
             }
         }
 
-        // P = exp2(s c - m) rounded to bf16 (the PV operand); l += the rounded values
-        bf16x8 pf[QB][NB][2];
+        // P = exp2(s c - m) rounded to bf16 (the PV operand); l += the rounded
+        // values. Lane slot j of the P^T of 16 keys kk holds key
+        // 16kk + 8(j/4) + 4hh + j%4.
+        bf16x8 pf[QB][NB * 2];
+        float mneg[QB];
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const float mref = m_used[qb] == -INFINITY ? 0.0f : m_used[qb];
+        for (int qb = 0; qb < QB; ++qb) mneg[qb] = m_used[qb] == -INFINITY ? 0.0f : -m_used[qb];
+        auto exps = [&](int kk, int j0, int j1) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int j = j0; j < j1; j += 2)
 #pragma unroll
-                for (int i = 0; i < 16; i += 2) {
-                    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qb][b][i], c, -mref));
-                    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qb][b][i + 1], c, -mref));
+                for (int qb = 0; qb < QB; ++qb) {
+                    const f32x16& sb = s[qb][kk >> 1];
+                    const int i = 8 * (kk & 1) + j;
+                    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sb[i], c, mneg[qb]));
+                    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sb[i + 1], c, mneg[qb]));
                     const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
-                    l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16x2{(__bf16)1.0f, (__bf16)1.0f},
-                                                                l_run[qb], false);
-                    pf[qb][b][i >> 3][i & 7] = pp[0];
-                    pf[qb][b][i >> 3][(i & 7) + 1] = pp[1];
+                    l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run[qb], false);
+                    pf[qb][kk][j] = pp[0];
+                    pf[qb][kk][j + 1] = pp[1];
                 }
+        };
+        exps(0, 0, 8);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NV; ++n) {
+            const int kk = n / MB, mb = n % MB;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+                o[qb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[(NK + n) % RA], pf[qb][kk], o[qb][mb], 0, 0, 0);
+            if (n + RA < NV) frag[(NK + n) % RA] = read_frag(NK + n + RA);
+            if (kk + 1 < NB * 2) exps(kk + 1, mb * 8 / MB, (mb + 1) * 8 / MB);
+            __builtin_amdgcn_sched_barrier(0);
         }
-
-        // lane slot j of P^T holds key 16kk + 8(j/4) + 4hh + j%4; each V
-        // fragment feeds the QB query blocks
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    const uint8_t* vp = vb + (b * 32 + kk * 16) * ROWB + voff[mb];
-                    const bf16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS bf16x4*)(vp));
-                    const bf16x4 vc = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS bf16x4*)(vp + 8 * ROWB));
-                    const bf16x8 vf = {va[0], va[1], va[2], va[3], vc[0], vc[1], vc[2], vc[3]};
-#pragma unroll
-                    for (int qb = 0; qb < QB; ++qb)
-                        o[qb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[qb][b][kk], o[qb][mb], 0, 0, 0);
-                }
     };
 
     // Stages st+1 .. st+NSTAGE-1 are in flight while stage st is computed.
     // Loads complete in order, so waiting for stage st leaves the later
     // stages outstanding.
-    constexpr int LPS = 2 * NJ;  // loads per stage per thread (K and V)
+    constexpr int LPS = 2 * IPP * PW;  // loads per stage per wave (K and V)
     const int full_stages = (kv_end - kv_begin) / STEP;  // stages with no key past the range
     auto wait_stage = [&](int st) {
         const int later = min(NSTAGE - 2, nstages - 1 - st);  // stages issued after st
@@ -583,29 +590,46 @@ __global__ __launch_bounds__(64 * QW * KW, MINB) void attn_tiles_kernel(AttnArgs
         else
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
+    // The compiler does not see the copies, so it would make the first use of
+    // Q wait for every one in flight: Q is waited for here, with the page ids
+    // or the first stage, which are needed at this point anyway.
+    auto wait_q = [&]() {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int s = 0; s < DS; ++s) asm volatile("" : "+v"(qf[qb][s]));
+    };
+    if (NSTAGE > 2) wait_q();
+    // the next 64 page ids, once stage st has read the last of these
+    auto next_pages = [&](int st) {
+        if (!all_fresh && ((st + 1) * SP & 63) == 0 && (st + 1) * SP < npg) load_pages((st + 1) * SP);
+    };
+    // the write-back's pages: loaded before the first copies, kept in LDS after
+    const int nwp = writer ? plist ? it.n : ((wb_hi + 15) >> 4) - wpg0 : 0;
+    int32_t wpage = 0;
+    if (tid < nwp) wpage = a.page_ids[it.page_start + (plist ? lpos >> 4 : wpg0 + tid)];
     for (int k = 0; k < NSTAGE - 1 && k < nstages; ++k) issue_stage(k, k);
-    if (writer && !plist && tid < ((wb_hi + 15) >> 4) - wpg0) wpages[tid] = a.page_ids[it.page_start + wpg0 + tid];
+    if (NSTAGE == 2) wait_q();
+    if (tid < nwp) {
+        wpages[tid] = wpage;
+        if (plist) fpos[tid] = lpos;
+    }
     int st = 0;
     for (; st < full_stages; ++st) {
         wait_stage(st);
         __syncthreads();
-        if (st + NSTAGE - 1 < nstages) issue_stage(st + NSTAGE - 1, (st + NSTAGE - 1) % NSTAGE);
-        if (writer) write_back(st);
-        if (head_ok) {  // a wave past its tile's GQA group only stages and writes back
-            f32x16 sc[QB][NB];
-            qk(st, sc);
-            softmax_pv(st, sc, false);
+        if (st + NSTAGE - 1 < nstages) {
+            issue_stage(st + NSTAGE - 1, (st + NSTAGE - 1) % NSTAGE);
+            next_pages(st + NSTAGE - 1);
         }
+        if (writer) write_back(st);
+        if (head_ok) attend(st, std::false_type{});  // a wave past its tile's GQA group only stages and writes back
     }
     if (st < nstages) {  // the last, partial stage
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (writer) write_back(st);
-        if (head_ok) {
-            f32x16 sc[QB][NB];
-            qk(st, sc);
-            softmax_pv(st, sc, true);
-        }
+        if (head_ok) attend(st, std::true_type{});
     }
 
     // ---- combine the context sub-ranges of the waves that share query rows
@@ -793,8 +817,7 @@ hipError_t launch(const void* fn, dim3 grid, unsigned threads, Args args, hipStr
 
 template <int D, int QW, int KW, int QB, int NB, bool HA, int NSTAGE = 2>
 hipError_t launch_tiles(const AttnArgs& args, int n_tiles, hipStream_t stream, LaunchEvents ev) {
-    constexpr int MINB = min_blocks_per_cu<D, QW, KW, QB, NB, NSTAGE>();
-    return launch(reinterpret_cast<const void*>(&attn_tiles_kernel<D, QW, KW, QB, NB, NSTAGE, HA, MINB>),
+    return launch(reinterpret_cast<const void*>(&attn_tiles_kernel<D, QW, KW, QB, NB, NSTAGE, HA>),
                   dim3(unsigned(n_tiles)), unsigned(64 * QW * KW), args, stream, ev);
 }
 
