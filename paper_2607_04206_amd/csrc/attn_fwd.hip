@@ -27,7 +27,10 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <atomic>
 #include <mutex>
+#include <random>
 #include <string>
 #include <type_traits>
 
@@ -70,6 +73,7 @@ struct AttnArgs {
     int32_t hq;
     int32_t hkv;
     float scale_log2;
+    uint64_t nonce;  // marks this call's split partials as written; 0: merge_kernel combines them
 };
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -168,6 +172,33 @@ __device__ __forceinline__ float half_sum(float x) {
 // because O and l always share the same reference.
 constexpr float kRescaleThreshold = 8.0f;
 
+// Split partials cross the XCDs, whose L2s are not coherent: stores write
+// through to memory and loads bypass the L2 (agent scope, sc1).
+__device__ __forceinline__ void store_agent(float* p, float4 v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
+}
+__device__ __forceinline__ void store_agent(float* p, float v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float load_agent(const float* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+constexpr int kBufferAgent = 16;  // sc1 in a buffer load's cache policy
+
+// Whether the last tile to finish merges an item's S partials, given the
+// query waves qw of its tiles; else merge_kernel does. The tile reads S * qw
+// partials of 16 KiB (D = 128) by itself, the launch reads all in parallel but
+// costs 4 to 8 us with its gap. Measured, launch -> in the tile: 28/4 heads
+// (qw 4) one decode in 8 splits 18.2 -> 17.8 us, 8 decodes in 4 19.8 -> 17.4
+// and in 8 29.2 -> 30.3, 4 decodes in 12 27.6 -> 30.3; whole groups (qw 7)
+// 24 decodes in 4 70 -> 63; 32/32 heads (qw 1) one decode in 12 22.3 -> 18.4
+// and in 16 27.8 -> 22.2.
+constexpr int kMaxMergeInTile = 16;
+constexpr int kMaxMergePartials = 28;
+__host__ __device__ constexpr int max_merge_in_tile(int qw) {
+    return kMaxMergePartials / qw < kMaxMergeInTile ? kMaxMergePartials / qw : kMaxMergeInTile;
+}
+
 // Waves per SIMD the register budget is sized for: two (256 registers) when a
 // wave holds one query block.
 constexpr int waves_per_simd(int qb) { return qb == 1 ? 2 : 1; }
@@ -201,8 +232,9 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
     constexpr int MERGE_REGS = MB * 16 + 2;
     static_assert(KW == 1 || QB == 1, "context-splitting waves hold one query block");
     static_assert(!HEADS_ACROSS || QB == 1, "a decode block is 32 rows");
-    static_assert(KW == 1 || (QW * (KW - 1) * MERGE_REGS * 64 * 4) <= 2 * NSTAGE * TILE,
+    static_assert(KW == 1 || (QW * KW * MERGE_REGS * 64 * 4) <= 2 * NSTAGE * TILE,
                   "cross-wave merge must fit in the stage buffers");
+    static_assert(MB % KW == 0, "the waves of a query slot share its dims");
     static_assert(NSTAGE >= 2 && NSTAGE <= 4, "2 to 4 stage buffers");
     // pages a tile's write-back can touch: its rows at any offset, or one per listed row
     constexpr int WPAGES = HEADS_ACROSS || (32 * QB * QW + 15) / 16 + 1 < kWaveRows ? kWaveRows : (32 * QB * QW + 15) / 16 + 1;
@@ -213,6 +245,7 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
     static_assert(64 % SP == 0 && (NSTAGE - 1) * SP < 64, "a stage's page ids sit in one register of 64 lanes");
 
     __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * NSTAGE * TILE];
+    __shared__ bool merging;  // this tile merges its rows' splits
     __shared__ int32_t fpos[kWaveRows];   // the listed positions (kItemPosList items)
     __shared__ int32_t wpages[WPAGES];  // pages of the fresh rows this tile writes back
 
@@ -235,6 +268,8 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
     const bool head_ok = head_want < (t.kv_head + 1) * (a.hq / a.hkv);
     const int head = head_ok ? head_want : t.q_head0;
     const int row_base = across ? t.row0 : t.row0 + 32 * QB * qs;
+    const bool split_out = it.num_splits > 1;  // fp32 partials go to the workspace
+    const bool merge_here = split_out && a.nonce != 0 && it.num_splits <= max_merge_in_tile(QW);
     const int kv_begin = t.kv_begin, kv_end = t.kv_end;
     const int nstages = (kv_end - kv_begin + STEP - 1) / STEP;
     // a whole prefill brings every position fresh: no page lookups
@@ -255,8 +290,8 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
         if (plist) iv = a.page_info[k];
     };
     if (!all_fresh) load_pages(0);
-    int32_t lpos = 0;  // the listed position of row tid
-    if (plist && tid < it.n) lpos = a.positions[it.pos_start + tid];
+    int32_t lpos = 0;  // the listed position of row `lane`, in every wave
+    if (plist) lpos = a.positions[it.pos_start + min(lane, it.n - 1)];
 
     // ---- Q fragments (B operand: k = dims, n = query). Lanes past the last
     // row hold row 0 again: a query is a column of every product, so they
@@ -395,14 +430,15 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
         if (lo >= hi) return;
         const uint8_t* kb = smem + (st % NSTAGE) * 2 * TILE;
         const uint8_t* vb = kb + TILE;
-        if (plist) {  // the listed positions inside [lo, hi)
-            for (int cidx = tid; cidx < it.n * NC; cidx += NT) {
-                const int p = fpos[cidx / NC], pos = cidx % NC;
-                if (p < lo || p >= hi) continue;
+        if (plist) {  // the listed positions inside [lo, hi): a run of the list
+            const uint64_t in = __builtin_amdgcn_ballot_w64(lane < it.n && lpos >= lo && lpos < hi);
+            const int first = __builtin_ctzll(in | 1ull << 63), count = __builtin_popcountll(in);
+            for (int cidx = tid; cidx < count * NC; cidx += NT) {
+                const int row = first + cidx / NC, p = fpos[row], pos = cidx % NC;
                 const int r = p - key0;
                 const u32x4 kv = *(const LDS u32x4*)(kb + r * ROWB + ((pos ^ swz_k<D>(r)) << 4));
                 const u32x4 vv = *(const LDS u32x4*)(vb + r * ROWB + ((pos ^ swz_v<D>(r)) << 4));
-                const size_t dst = (((size_t)wpages[cidx / NC] * a.hkv + t.kv_head) * 16 + (p & 15)) * D + pos * 8;
+                const size_t dst = (((size_t)wpages[row] * a.hkv + t.kv_head) * 16 + (p & 15)) * D + pos * 8;
                 *(u32x4*)(a.k_cache + dst) = kv;
                 *(u32x4*)(a.v_cache + dst) = vv;
             }
@@ -632,56 +668,173 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
         if (head_ok) attend(st, std::true_type{});
     }
 
-    // ---- combine the context sub-ranges of the waves that share query rows
+    // ---- combine the context sub-ranges of the waves that share query rows:
+    // each of the KW waves then holds MBW of the MB 32-dim blocks of O
+    constexpr int MBW = MB / KW;
+    const int mb0 = ks * MBW;  // first block of this wave
     if constexpr (KW > 1) {
         __syncthreads();
-        float* mbuf = reinterpret_cast<float*>(smem);
-        if (ks > 0) {
-            float* dst = mbuf + (size_t)((qs * (KW - 1) + (ks - 1)) * MERGE_REGS) * 64;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dst[(mb * 16 + i) * 64 + lane] = o[0][mb][i];
-            dst[(MB * 16) * 64 + lane] = m_used[0];
-            dst[(MB * 16 + 1) * 64 + lane] = l_run[0];
-        }
-        __syncthreads();
-        if (ks > 0) return;
-        float m_tot = m_used[0];
-#pragma unroll
-        for (int k = 1; k < KW; ++k) {
-            const float* src = mbuf + (size_t)((qs * (KW - 1) + (k - 1)) * MERGE_REGS) * 64;
-            m_tot = fmaxf(m_tot, src[(MB * 16) * 64 + lane]);
-        }
-        // wave ks = 0 always holds a valid key, so m_tot is finite
-        const float sc0 = __builtin_amdgcn_exp2f(m_used[0] - m_tot);
-        l_run[0] *= sc0;
+        float* mbuf = reinterpret_cast<float*>(smem) + (size_t)qs * KW * MERGE_REGS * 64;
+        float* mine = mbuf + (size_t)ks * MERGE_REGS * 64;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o[0][mb][i] *= sc0;
+            for (int i = 0; i < 16; ++i) mine[(mb * 16 + i) * 64 + lane] = o[0][mb][i];
+        mine[(MB * 16) * 64 + lane] = m_used[0];
+        mine[(MB * 16 + 1) * 64 + lane] = l_run[0];
+        __syncthreads();
+        float m_tot = -INFINITY;
 #pragma unroll
-        for (int k = 1; k < KW; ++k) {
-            const float* src = mbuf + (size_t)((qs * (KW - 1) + (k - 1)) * MERGE_REGS) * 64;
+        for (int k = 0; k < KW; ++k) m_tot = fmaxf(m_tot, mbuf[(size_t)(k * MERGE_REGS + MB * 16) * 64 + lane]);
+        // wave ks = 0 always holds a valid key, so m_tot is finite
+        l_run[0] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) {
+            const float* src = mbuf + (size_t)k * MERGE_REGS * 64;
             const float sck = __builtin_amdgcn_exp2f(src[(MB * 16) * 64 + lane] - m_tot);
-            l_run[0] += sck * src[(MB * 16 + 1) * 64 + lane];
+            l_run[0] = k == 0 ? sck * src[(MB * 16 + 1) * 64 + lane] : l_run[0] + sck * src[(MB * 16 + 1) * 64 + lane];
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) o[0][mb][i] += sck * src[(mb * 16 + i) * 64 + lane];
+                for (int i = 0; i < 16; ++i) {
+                    const float v = sck * src[((mb0 + mb) * 16 + i) * 64 + lane];
+                    o[0][mb][i] = k == 0 ? v : o[0][mb][i] + v;
+                }
         }
         m_used[0] = m_tot;
     }
 
-    // ---- epilogue
-    // Rows written straight to `out` leave through LDS where it holds them:
-    // each lane stages its query's dims in 8-byte pieces, then 16 consecutive
-    // lanes store one whole row in 16-byte pieces (stored directly, one
-    // instruction would leave 16-byte fragments of 32 rows).
+    // ---- epilogue: O / l and the LSE, to the output or as a split's partial
+    float lse_val[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const float l_tot = half_sum(l_run[qb]);
+        const float inv = 1.0f / l_tot;
+        lse_val[qb] = m_used[qb] * 0.69314718055994530942f + logf(l_tot);
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[qb][mb][i] *= inv;
+    }
+    if (split_out) {
+        if (!merge_here) {
+            // rows of D for merge_kernel: [split][row][head]
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const int row = row_base + 32 * qb + qn;
+                if (!head_ok || row >= it.n) continue;
+                const size_t prow = (size_t)(t.split * it.n + row) * a.hq + head;
+                float* po = a.ws + it.ws_o + prow * D;
+#pragma unroll
+                for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4)
+                        *(float4*)(po + (mb0 + mb) * 32 + 8 * q4 + 4 * hh) =
+                            float4{o[qb][mb][4 * q4], o[qb][mb][4 * q4 + 1], o[qb][mb][4 * q4 + 2], o[qb][mb][4 * q4 + 3]};
+                if (hh == 0 && ks == 0) a.ws[it.ws_lse + prow] = lse_val[qb];
+            }
+            return;
+        }
+        // For a merge by a tile like this one: [split][head][rows of 32]
+        // [D / 4][row] float4 and [split][head][row] LSE, so that a wave's
+        // store, and its load by the merging wave, of one register is 16-byte
+        // pieces of consecutive rows.
+        const size_t rows0 = (size_t)(t.split * a.hq + head) * it.n;  // rows before this (split, head)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const int r0 = row_base + 32 * qb, nb = min(32, it.n - r0);
+            if (!head_ok || qn >= nb) continue;
+            float* po = a.ws + it.ws_o + (rows0 + r0) * D;
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const int d4 = (mb0 + mb) * 8 + q4 * 2 + hh;
+                    const float4 v = {o[qb][mb][4 * q4], o[qb][mb][4 * q4 + 1], o[qb][mb][4 * q4 + 2], o[qb][mb][4 * q4 + 3]};
+                    store_agent(po + (size_t)(d4 * nb + qn) * 4, v);
+                }
+            if (hh == 0 && ks == 0) store_agent(a.ws + it.ws_lse + rows0 + r0 + qn, lse_val[qb]);
+        }
+        // The tile that finds every split of its rows written merges them.
+        // Each tile marks its split with the call's nonce, then looks at all
+        // marks: both are read-modify-writes, complete before the next, so
+        // the last tile to mark finds all of them. Two tiles may, and then
+        // write the same bits. The merging tile clears the marks, so that a
+        // replayed graph, whose nonce repeats, starts from none; whatever
+        // else the workspace held is not this call's 64-bit nonce.
+        uint64_t* marks = reinterpret_cast<uint64_t*>(a.ws + merge_marks(it, a.hq)) +
+                          (size_t)((t.row0 / kWaveRows) * a.hq + t.q_head0) * it.num_splits;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's partials are in memory
+        __syncthreads();
+        if (wave == 0) {
+            uint64_t before = 0, none = 0;
+            if (lane == 0) before = __hip_atomic_exchange(marks + t.split, a.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" : "+v"(before), "+v"(none)::"memory");
+            bool there = true;
+            if (lane < it.num_splits)
+                there = __hip_atomic_fetch_or(marks + lane, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.nonce;
+            const bool all = __builtin_amdgcn_ballot_w64(there) == ~0ull;
+            if (all && lane < it.num_splits)
+                __hip_atomic_store(marks + lane, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0) merging = all;
+        }
+        __syncthreads();
+        if (!merging) return;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const int r0 = row_base + 32 * qb, nb = min(32, it.n - r0);
+            if (!head_ok || nb <= 0) continue;
+            const int row = min(qn, nb - 1);  // lanes past the last row repeat it
+            const size_t step = (size_t)a.hq * it.n;  // rows between splits
+            const size_t first = (size_t)head * it.n + r0;
+            float ls[kMaxMergeInTile], mx = -INFINITY;
+#pragma unroll
+            for (int k = 0; k < kMaxMergeInTile; ++k)
+                if (k < it.num_splits) ls[k] = load_agent(a.ws + it.ws_lse + k * step + first + row);
+#pragma unroll
+            for (int k = 0; k < kMaxMergeInTile; ++k)
+                if (k < it.num_splits) mx = fmaxf(mx, ls[k]);
+            f32x16 acc[MBW];
+            float tot = 0.0f;
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[mb][i] = 0.0f;
+#pragma unroll 2
+            for (int k = 0; k < it.num_splits; ++k) {
+                const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    a.ws + it.ws_o + (k * step + first) * D, 0, nb * D * 4, 0x00027000);
+                u32x4 v[MBW * 4];
+#pragma unroll
+                for (int j = 0; j < MBW * 4; ++j) {
+                    const int d4 = (mb0 + j / 4) * 8 + (j & 3) * 2 + hh;
+                    v[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (d4 * nb + row) * 16, 0, kBufferAgent);
+                }
+                float w = 0.0f;
+#pragma unroll
+                for (int m = 0; m < kMaxMergeInTile; ++m)
+                    if (m == k) w = __expf(ls[m] - mx);
+                tot += w;
+#pragma unroll
+                for (int j = 0; j < MBW * 4; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[j / 4][4 * (j & 3) + e] += w * __uint_as_float(v[j][e]);
+            }
+            const float inv = 1.0f / tot;
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[qb][mb][i] = acc[mb][i] * inv;
+            lse_val[qb] = mx + logf(tot);
+        }
+    }
+    // Output rows leave through LDS where it holds them: each lane stages its
+    // query's dims in 8-byte pieces, then 16 consecutive lanes store one whole
+    // row in 16-byte pieces (stored directly, one instruction would leave
+    // 16-byte fragments of 32 rows).
     constexpr int EROW = D * 2 + 16;  // bytes per staged row: 16-byte aligned, shifted by four banks
-    constexpr int EBASE = KW > 1 ? QW * (KW - 1) * MERGE_REGS * 64 * 4 : 0;  // past the merge data
+    constexpr int EBASE = KW > 1 ? QW * KW * MERGE_REGS * 64 * 4 : 0;  // past the waves' partials
     constexpr bool ESTAGE = EBASE + QW * QB * 32 * EROW <= 2 * NSTAGE * TILE;
-    const bool split_out = it.num_splits > 1;  // split partials go to the workspace in fp32
     if constexpr (ESTAGE && KW == 1) {
         if (!split_out) __syncthreads();  // every wave is past its last stage's reads
     }
@@ -689,62 +842,31 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const int row = row_base + 32 * qb + qn;
-        const float l_tot = half_sum(l_run[qb]);
-        const float inv = 1.0f / l_tot;
-        const float lse_val = m_used[qb] * 0.69314718055994530942f + logf(l_tot);
-        if (ESTAGE && !split_out) {
+        const bool stored = row < it.n && head_ok;
+        uint16_t* op = a.out + ((size_t)(it.q_start + row) * a.hq + head) * D;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const int dim = mb * 32 + 8 * q4 + 4 * hh;
-                    const bf16x4 v = {(__bf16)(o[qb][mb][4 * q4] * inv), (__bf16)(o[qb][mb][4 * q4 + 1] * inv),
-                                      (__bf16)(o[qb][mb][4 * q4 + 2] * inv),
-                                      (__bf16)(o[qb][mb][4 * q4 + 3] * inv)};
-                    *(LDS u32x2*)(ebuf + (32 * qb + qn) * EROW + dim * 2) = __builtin_bit_cast(u32x2, v);
-                }
-            if (row < it.n && head_ok && hh == 0 && a.lse) a.lse[(size_t)(it.q_start + row) * a.hq + head] = lse_val;
-            continue;
-        }
-        if (row >= it.n || !head_ok) continue;
-        if (split_out) {
-            const size_t prow = (size_t)(t.split * it.n + row) * a.hq + head;
-            float* po = a.ws + it.ws_o + prow * D;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const int dim = mb * 32 + 8 * q4 + 4 * hh;
-                    float4 v = {o[qb][mb][4 * q4] * inv, o[qb][mb][4 * q4 + 1] * inv,
-                                o[qb][mb][4 * q4 + 2] * inv, o[qb][mb][4 * q4 + 3] * inv};
-                    *(float4*)(po + dim) = v;
-                }
-            if (hh == 0) a.ws[it.ws_lse + prow] = lse_val;
-        } else {
-            uint16_t* op = a.out + ((size_t)(it.q_start + row) * a.hq + head) * D;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const int dim = mb * 32 + 8 * q4 + 4 * hh;
-                    const bf16x4 v = {(__bf16)(o[qb][mb][4 * q4] * inv), (__bf16)(o[qb][mb][4 * q4 + 1] * inv),
-                                      (__bf16)(o[qb][mb][4 * q4 + 2] * inv),
-                                      (__bf16)(o[qb][mb][4 * q4 + 3] * inv)};
-                    *(u32x2*)(op + dim) = __builtin_bit_cast(u32x2, v);
-                }
-            if (hh == 0 && a.lse) a.lse[(size_t)(it.q_start + row) * a.hq + head] = lse_val;
-        }
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int dim = (mb0 + mb) * 32 + 8 * q4 + 4 * hh;
+                const bf16x4 v = {(__bf16)o[qb][mb][4 * q4], (__bf16)o[qb][mb][4 * q4 + 1],
+                                  (__bf16)o[qb][mb][4 * q4 + 2], (__bf16)o[qb][mb][4 * q4 + 3]};
+                if (ESTAGE) *(LDS u32x2*)(ebuf + (32 * qb + qn) * EROW + dim * 2) = __builtin_bit_cast(u32x2, v);
+                else if (stored) *(u32x2*)(op + dim) = __builtin_bit_cast(u32x2, v);
+            }
+        if (stored && hh == 0 && ks == 0 && a.lse) a.lse[(size_t)(it.q_start + row) * a.hq + head] = lse_val[qb];
     }
     if constexpr (ESTAGE) {
-        if (!split_out && head_ok) {
-            // the wave reads back only rows it staged itself
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        // with one wave per query slot a wave reads back only rows it staged
+        if constexpr (KW > 1) __syncthreads();
+        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (head_ok) {
             constexpr int CPR = D / 8;           // 16-byte pieces per row
-            constexpr int NCE = QB * 32 * CPR;   // pieces per wave
-            static_assert(NCE % 64 == 0, "whole rounds of 64 lanes");
+            constexpr int NCE = QB * 32 * CPR;   // pieces per query slot
+            static_assert(NCE % (64 * KW) == 0, "whole rounds of 64 lanes");
 #pragma unroll
-            for (int j = 0; j < NCE / 64; ++j) {
-                const int c = j * 64 + lane;
+            for (int j = 0; j < NCE / (64 * KW); ++j) {
+                const int c = (j * KW + ks) * 64 + lane;
                 const int r = c / CPR, col = c % CPR;  // staged row r is row row_base + r
                 if (row_base + r < it.n) {
                     const u32x4 v = *(const LDS u32x4*)(ebuf + r * EROW + col * 16);
@@ -764,15 +886,20 @@ struct MergeArgs {
     float* lse;
     int32_t hq;
     int32_t d;
+    // splits up to which the tiles merge items of more than kWaveRows rows, and block decodes
+    int32_t rows_in_tile;
+    int32_t block_in_tile;
 };
 
 // grid: (merge row, 256-element slice of the row's Hq x D/4 float4 outputs);
 // one thread per float4 of one head, so that every partial of a row is
-// loaded by a different thread in parallel
+// loaded by a different thread in parallel. Items that the tiles merge
+// themselves are left out.
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     const MergeRow mr = a.rows[blockIdx.x];
     const ItemRec it = a.items[mr.item];
     const int S = it.num_splits;
+    if (S <= (it.n > kWaveRows ? a.rows_in_tile : a.block_in_tile)) return;
     const int d4n = a.d / 4;
     const int e = blockIdx.y * 256 + threadIdx.x;
     if (e >= a.hq * d4n) return;
@@ -842,6 +969,23 @@ hipError_t launch_decode(const AttnArgs& args, int n_tiles, int qw, int kw, int 
     return hipSuccess;
 }
 
+// A number no other call and no leftover memory holds: a mixed counter that
+// starts at a random place in each process; never 0.
+uint64_t next_nonce() {
+    static const uint64_t seed = [] {
+        std::random_device rd;
+        return uint64_t(rd()) << 32 | rd();
+    }();
+    static std::atomic<uint64_t> calls{0};
+    for (;;) {
+        uint64_t x = seed + calls.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
+        x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;  // splitmix64 (Steele, Lea, Flood, 2014), a bijection
+        x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+        x ^= x >> 31;
+        if (x) return x;
+    }
+}
+
 sangam_status hip_fail(hipError_t e, const char* what) {
     set_error(std::string(what) + ": " + hipGetErrorString(e));
     return SANGAM_ERR_HIP;
@@ -858,8 +1002,11 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // for the symbol: kernels receive the device address that hipGetSymbolAddress
 // returns for the current device, cached per device below.
 namespace {
-constexpr size_t kScratchBytes = size_t(32) << 20;
-static __device__ __align__(256) uint8_t scratch[kScratchBytes];
+constexpr size_t kScratchBytes = size_t(32) << 20;  // partials it holds
+// beside them the merge marks of any plan with that many bytes of partials
+// (at worst 256 bytes of marks to 768 of partials: two splits of one row)
+constexpr size_t kScratchMarks = kScratchBytes / 3 + 4096;
+static __device__ __align__(256) uint8_t scratch[kScratchBytes + kScratchMarks];
 
 constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
@@ -928,14 +1075,14 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
     }
     if (use_scratch && h->workspace_bytes > 0) {
         // the allocation-free entry point: split partials go to the scratch array
-        if (size_t(h->workspace_bytes) > kScratchBytes) {
-            set_error("the plan's split partials need " + std::to_string(h->workspace_bytes) +
+        if (size_t(h->workspace_bytes - h->mark_bytes) > kScratchBytes || size_t(h->mark_bytes) > kScratchMarks) {
+            set_error("the plan's split partials need " + std::to_string(h->workspace_bytes - h->mark_bytes) +
                       " bytes; the allocation-free forward holds " + std::to_string(kScratchBytes));
             return SANGAM_ERR_BUFFER;
         }
         if (sangam_status st = scratch_address(static_cast<hipStream_t>(stream_ptr), &workspace); st != SANGAM_OK)
             return st;
-        workspace_bytes = kScratchBytes;
+        workspace_bytes = kScratchBytes + kScratchMarks;
     }
     if (h->workspace_bytes > 0) {
         if (!workspace || workspace_bytes < size_t(h->workspace_bytes)) {
@@ -983,7 +1130,8 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
                   reinterpret_cast<const uint32_t*>(pd + h->off_page_info),
                   h->hq,
                   h->hkv,
-                  h->scale_log2};
+                  h->scale_log2,
+                  h->mark_bytes > 0 ? next_nonce() : 0};
 
     // 1. attention: prefill-shaped tiles (compute-bound) first, then
     // decode-shaped tiles; both also write the fresh rows into their pages
@@ -1020,15 +1168,20 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
         return hip_fail(e, "event record");
     }
 
-    // 2. merge split contexts
-    if (h->n_merge_rows > 0) {
+    // 2. merge split contexts, those of the items that the tiles do not merge
+    const int prefill_qw = h->prefill_rows / kWaveRows;
+    const int rows_in_tile = args.nonce ? max_merge_in_tile(prefill_qw) : 0;
+    const int block_in_tile = args.nonce ? max_merge_in_tile(h->n_decode_tiles > 0 ? h->decode_qw : prefill_qw) : 0;
+    if (h->n_merge_rows > 0 && h->max_splits > std::min(rows_in_tile, block_in_tile)) {
         MergeArgs m{reinterpret_cast<const MergeRow*>(pd + h->off_merge),
                     items,
                     static_cast<const float*>(workspace),
                     static_cast<uint16_t*>(out),
                     lse,
                     h->hq,
-                    h->d};
+                    h->d,
+                    rows_in_tile,
+                    block_in_tile};
         const unsigned slices = unsigned((h->hq * (h->d / 4) + 255) / 256);
         hipError_t e = launch(reinterpret_cast<const void*>(&merge_kernel), dim3(unsigned(h->n_merge_rows), slices),
                               256u, m, stream, evs(2));

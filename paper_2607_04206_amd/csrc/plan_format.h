@@ -38,8 +38,8 @@ struct ItemRec {
     int32_t num_splits;  // context chunks (1 = written straight to out)
     int32_t split_len;   // keys per chunk (multiple of kKeyAlign), last may be shorter
     int32_t merge_base;  // first merge row of the item, -1 when not split
-    int64_t ws_o;        // float offset of partial O  [num_splits][n][Hq][D]
-    int64_t ws_lse;      // float offset of partial LSE [num_splits][n][Hq]
+    int64_t ws_o;        // float offset of num_splits x n x Hq x D floats of partial O
+    int64_t ws_lse;      // float offset of num_splits x n x Hq partial LSE; merge_marks follow
     int32_t flags;       // kItemPosList or 0
     int32_t pos_start;   // first entry of the item's positions (kItemPosList)
 };
@@ -113,7 +113,7 @@ struct PlanHeader {
     int32_t max_splits;
     int32_t prefill_rows;  // query rows per prefill-shaped tile: kPrefillRows or kWidePrefillRows
     int32_t n_fused_decode_tiles;
-    int32_t reserved;
+    int32_t mark_bytes;  // of the workspace: merge marks (0 in older plans, which have none)
     int64_t workspace_bytes;
 
     uint64_t off_items;
@@ -123,6 +123,19 @@ struct PlanHeader {
     uint64_t off_positions;  // int32 positions of kItemPosList items
     uint64_t off_page_info;  // uint32 per page (page_indptr order), when any item is kItemPosList
 };
+
+// Merge marks of a split item: per 32-row block, query head and split one
+// uint64 (a tile uses those of its first block and head), after the item's
+// partial LSE in the workspace. Float offset, and their number of floats.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int64_t merge_marks(const ItemRec& it, int hq) {
+    return it.ws_lse + (int64_t(it.num_splits) * it.n * hq + 63) / 64 * 64;
+}
+inline int64_t merge_mark_floats(const ItemRec& it, int hq) {
+    return (int64_t(it.n + kWaveRows - 1) / kWaveRows * hq * it.num_splits * 2 + 63) / 64 * 64;
+}
 
 static_assert(sizeof(ItemRec) == 56, "ItemRec layout is part of the blob format");
 static_assert(sizeof(TileRec) == 32, "TileRec layout is part of the blob format");
