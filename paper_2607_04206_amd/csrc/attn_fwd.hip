@@ -228,6 +228,12 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
     constexpr int IPP = 16 / RPI;        // copy instructions per page
     constexpr int DS = D / 16;           // k-steps of the QK^T contraction
     constexpr int MB = D / 32;           // 32-dim blocks of O^T
+    // MFMAs at raised wave priority: those of QK^T (1), of PV (2) or none (0).
+    // Two waves share a SIMD. Measured: 128-key stages QK^T (long prefills
+    // 6,510 us with PV, 6,480 with it), 64-key ones PV (Dream mixed batch 261
+    // us with QK^T or none, 255 with it), D = 64 none (mixed batch 80.9 us
+    // with PV, 76.4 without).
+    constexpr int PRIO = D == 64 ? 0 : NB == 4 ? 1 : 2;
     constexpr int RA = 4;                // steps between a fragment's LDS read and its MFMA
     constexpr int MERGE_REGS = MB * 16 + 2;
     static_assert(KW == 1 || QB == 1, "context-splitting waves hold one query block");
@@ -283,7 +289,6 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
     // reads its ids with v_readlane, with no LDS or barrier in between.
     int32_t pv = 0;
     uint32_t iv = 0;
-    uint64_t listed = 0;  // the pages among those 64 with listed positions
     auto load_pages = [&](int first) {
         const int k = it.page_start + pg0 + min(first + lane, npg - 1);
         pv = a.page_ids[k];
@@ -334,18 +339,25 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
         foff_v[j] = uint32_t(r) * row_bytes - 1024 * j + cv;
     }
 
+    // stages [mixed0, mixed1) may hold fresh rows beside cached ones (a block's,
+    // or from the first to the last listed position), full_stages and on a
+    // partial page
+    const int last_pos = plist ? a.positions[it.pos_start + it.n - 1] : it.o + it.n - 1;
+    const int full_stages = (kv_end - kv_begin) / STEP;
+    const int mixed0 = all_fresh ? full_stages : min(full_stages, max(0, it.o - kv_begin) / STEP);
+    const int mixed1 = all_fresh ? full_stages : last_pos < kv_begin ? 0 : (last_pos - kv_begin) / STEP + 1;
+    const uint16_t* kfresh_w = kfresh + (int64_t)(kv_begin + wave * 16) * (int64_t)row_stride;
+    const uint16_t* vfresh_w = vfresh + (int64_t)(kv_begin + wave * 16) * (int64_t)row_stride;
+    const size_t stage_stride = STEP * row_stride;  // elements
+
     auto issue_stage = [&](int st, int buf) __attribute__((always_inline)) {
         uint8_t* kb = smem + buf * 2 * TILE;
         uint8_t* vb = kb + TILE;
-        const int skey0 = kv_begin + st * STEP;
         const int pl0 = st * SP & 63;  // lane holding the id of the stage's first page
-        // a whole stage of fresh rows (whole prefills) or of cached rows:
-        // wave-uniform bases, precomputed lane offsets
-        const bool whole = skey0 + STEP <= kv_end;
-        if (plist && pl0 == 0) listed = __builtin_amdgcn_ballot_w64((iv & 0xFFFFu) != 0);
-        const bool cached = plist ? (listed >> pl0 & ((1ull << SP) - 1)) == 0
-                                  : !all_fresh && (skey0 + STEP <= it.o || skey0 >= it.o + it.n);
-        if (__builtin_expect(whole && (all_fresh || cached), 1)) {
+        if (__builtin_expect(st < mixed0 || (st >= mixed1 && st < full_stages), 1)) {
+            // a whole stage of one kind: wave-uniform bases, precomputed lane offsets
+            const uint16_t* kf = kfresh_w + (size_t)unsigned(st) * stage_stride;
+            const uint16_t* vf = vfresh_w + (size_t)unsigned(st) * stage_stride;
 #pragma unroll
             for (int i = 0; i < PW; ++i) {
                 const int k = wave + i * NW;  // page of the stage
@@ -353,17 +365,17 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
                 LDS void* kd = (LDS void*)(kb + k * 16 * ROWB);
                 LDS void* vd = (LDS void*)(vb + k * 16 * ROWB);
                 if (all_fresh) {
-                    const size_t off = (size_t)(skey0 + k * 16) * row_stride;
-                    copy_page(kfresh + off, foff_k, kd);
-                    copy_page(vfresh + off, foff_v, vd);
+                    copy_page(kf + i * NW * 16 * row_stride, foff_k, kd);
+                    copy_page(vf + i * NW * 16 * row_stride, foff_v, vd);
                 } else {
-                    const size_t off = (size_t)__builtin_amdgcn_readlane(pv, pl0 + k) * page_stride;
+                    const size_t off = size_t(uint32_t(__builtin_amdgcn_readlane(pv, pl0 + k))) * page_stride;
                     copy_page(kcache + off, coff_k, kd);
                     copy_page(vcache + off, coff_v, vd);
                 }
             }
             return;
         }
+        const int skey0 = kv_begin + st * STEP;
         for (int k = wave; k < SP; k += NW) {
             LDS void* kd = (LDS void*)(kb + k * 16 * ROWB);
             LDS void* vd = (LDS void*)(vb + k * 16 * ROWB);
@@ -419,11 +431,12 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
     // positions written: [wb_lo, wb_hi) for a block; for a position list (a
     // decode, so heads-across), its listed positions inside the span from the
     // first to the last listed position
-    const int last_pos = plist ? a.positions[it.pos_start + it.n - 1] : it.o + it.n - 1;
     const int wb_lo = max(kv_begin, it.o + (across ? 0 : t.row0));
     const int wb_hi = min(kv_end, across ? last_pos + 1 : it.o + min(it.n, t.row0 + 32 * QB * QW));
     const bool writer = wb_head && wb_lo < wb_hi;
     const int wpg0 = wb_lo >> 4;
+    const int wst0 = writer ? (wb_lo - kv_begin) / STEP : nstages;  // stages [wst0, wst1) hold such rows
+    const int wst1 = writer ? (wb_hi - 1 - kv_begin) / STEP + 1 : 0;
     auto write_back = [&](int st) {
         const int key0 = kv_begin + st * STEP;
         const int lo = max(wb_lo, key0), hi = min(wb_hi, key0 + STEP);
@@ -533,7 +546,7 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
         bf16x8 frag[RA];
 #pragma unroll
         for (int n = 0; n < RA; ++n) frag[n] = read_frag(n);
-        __builtin_amdgcn_s_setprio(1);
+        if (PRIO == 1) __builtin_amdgcn_s_setprio(1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int n = 0; n < NK; ++n) {
@@ -550,7 +563,7 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
             if (b > 0 && k >= 2) take_max(b - 1, (k - 2) * 16 / (DS - 2), (k - 1) * 16 / (DS - 2));
             __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_s_setprio(0);
+        if (PRIO == 1) __builtin_amdgcn_s_setprio(0);
         take_max(NB - 1, 0, 16);
 
         // The reference max moves (and O, l are rescaled) only when a score
@@ -599,6 +612,7 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
                 }
         };
         exps(0, 0, 8);
+        if (PRIO == 2) __builtin_amdgcn_s_setprio(1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int n = 0; n < NV; ++n) {
@@ -610,13 +624,13 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
             if (kk + 1 < NB * 2) exps(kk + 1, mb * 8 / MB, (mb + 1) * 8 / MB);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (PRIO == 2) __builtin_amdgcn_s_setprio(0);
     };
 
     // Stages st+1 .. st+NSTAGE-1 are in flight while stage st is computed.
     // Loads complete in order, so waiting for stage st leaves the later
     // stages outstanding.
     constexpr int LPS = 2 * IPP * PW;  // loads per stage per wave (K and V)
-    const int full_stages = (kv_end - kv_begin) / STEP;  // stages with no key past the range
     auto wait_stage = [&](int st) {
         const int later = min(NSTAGE - 2, nstages - 1 - st);  // stages issued after st
         if (NSTAGE >= 4 && later >= 2)
@@ -658,13 +672,13 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
             issue_stage(st + NSTAGE - 1, (st + NSTAGE - 1) % NSTAGE);
             next_pages(st + NSTAGE - 1);
         }
-        if (writer) write_back(st);
+        if (st >= wst0 && st < wst1) write_back(st);
         if (head_ok) attend(st, std::false_type{});  // a wave past its tile's GQA group only stages and writes back
     }
     if (st < nstages) {  // the last, partial stage
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (writer) write_back(st);
+        if (st >= wst0 && st < wst1) write_back(st);
         if (head_ok) attend(st, std::true_type{});
     }
 
