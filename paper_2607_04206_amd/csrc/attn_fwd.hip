@@ -73,7 +73,8 @@ struct AttnArgs {
     int32_t hq;
     int32_t hkv;
     float scale_log2;
-    uint64_t nonce;  // marks this call's split partials as written; 0: merge_kernel combines them
+    uint64_t nonce;        // marks this call's split partials as written
+    int32_t merge_splits;  // splits up to which the tiles merge an item (0: merge_kernel does)
 };
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -203,6 +204,15 @@ __host__ __device__ constexpr int max_merge_in_tile(int qw) {
 // wave holds one query block.
 constexpr int waves_per_simd(int qb) { return qb == 1 ? 2 : 1; }
 
+// LDS of a work-group
+template <int BYTES>
+struct TileShared {
+    __attribute__((aligned(1024))) uint8_t stages[BYTES];  // K and V stage buffers
+    int32_t wpages[kWaveRows];  // pages of the fresh rows this tile writes back
+    int32_t fpos[kWaveRows];    // the listed positions (kItemPosList items)
+    bool merging;               // this tile merges its rows' splits
+};
+
 // One work-group per plan tile: a context range [kv_begin, kv_end) of one
 // item and KV head against QW query slots x QB blocks of 32 rows per slot.
 //   D      head dim (64, 128)
@@ -213,15 +223,16 @@ constexpr int waves_per_simd(int qb) { return qb == 1 ? 2 : 1; }
 //          LDS feeds QB MFMAs, so QB = 2 halves LDS traffic per flop
 //   NB     32-key blocks per wave per stage
 //   NSTAGE K/V stage buffers in LDS (NSTAGE - 1 stages in flight)
-template <int D, int QW, int KW, int QB, int NB, int NSTAGE, bool HEADS_ACROSS>
-__global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_kernel(AttnArgs a) {
-    constexpr int NT = 64 * QW * KW;     // threads
+//   HELP   more waves, which only stage and write back
+template <int D, int QW, int KW, int QB, int NB, int NSTAGE, bool HEADS_ACROSS, int HELP, typename Shared>
+__device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, const ItemRec it, Shared& shared) {
+    constexpr int NT = 64 * (QW * KW + HELP);  // threads
     constexpr int KT = 32 * NB;          // keys per wave per stage
     constexpr int STEP = KT * KW;        // keys per stage
     constexpr int NC = D / 8;            // 16-byte chunks per key row
     constexpr int ROWB = D * 2;          // bytes per key row
     constexpr int TILE = STEP * ROWB;    // bytes of one staged K (or V) tile
-    constexpr int NW = QW * KW;          // waves
+    constexpr int NW = QW * KW + HELP;   // waves
     constexpr int SP = STEP / 16;        // 16-key pages per stage
     constexpr int PW = (SP + NW - 1) / NW;  // pages a wave copies per stage
     constexpr int RPI = 64 / NC;         // key rows per copy instruction
@@ -243,39 +254,37 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
     static_assert(MB % KW == 0, "the waves of a query slot share its dims");
     static_assert(NSTAGE >= 2 && NSTAGE <= 4, "2 to 4 stage buffers");
     // pages a tile's write-back can touch: its rows at any offset, or one per listed row
-    constexpr int WPAGES = HEADS_ACROSS || (32 * QB * QW + 15) / 16 + 1 < kWaveRows ? kWaveRows : (32 * QB * QW + 15) / 16 + 1;
-    static_assert(WPAGES <= NT, "one thread per write-back page id");
+    static_assert((32 * QB * QW + 15) / 16 + 1 <= kWaveRows && kWaveRows <= NT, "one thread per write-back page id");
     // with more than two buffers the wait counts loads, so every wave must
     // issue the same number per stage
     static_assert(NSTAGE == 2 || SP % NW == 0, "deeper pipelines need whole staging rounds");
     static_assert(64 % SP == 0 && (NSTAGE - 1) * SP < 64, "a stage's page ids sit in one register of 64 lanes");
 
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * NSTAGE * TILE];
-    __shared__ bool merging;  // this tile merges its rows' splits
-    __shared__ int32_t fpos[kWaveRows];   // the listed positions (kItemPosList items)
-    __shared__ int32_t wpages[WPAGES];  // pages of the fresh rows this tile writes back
+    static_assert(sizeof(shared.stages) >= 2 * NSTAGE * TILE, "the stage buffers");
+    uint8_t* const smem = shared.stages;
+    int32_t* const fpos = shared.fpos;
+    int32_t* const wpages = shared.wpages;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = uniform(tid >> 6);
-    const int qs = wave % QW;
-    const int ks = wave / QW;
+    const bool computes = HELP == 0 || wave < QW * KW;
+    const int qs = computes ? wave % QW : 0;
+    const int ks = computes ? wave / QW : 0;
     const int qn = lane & 31;   // query (column) this lane holds in each block
     const int hh = lane >> 5;   // half-wave
 
-    const TileRec t = a.tiles[blockIdx.x];
-    const ItemRec it = a.items[t.item];
     // heads across the waves: a decode-shaped work-group, or a block decode
     // cut into a prefill-shaped one (whose last tile of a GQA group may hold
     // fewer heads than waves: the extra waves only stage K/V, write back and
     // meet the barriers; they compute and store nothing)
     const bool across = HEADS_ACROSS || (t.flags & kTileHeadsAcross);
     const int head_want = across ? t.q_head0 + qs : t.q_head0;
-    const bool head_ok = head_want < (t.kv_head + 1) * (a.hq / a.hkv);
+    const bool head_ok = computes && head_want < (t.kv_head + 1) * (a.hq / a.hkv);
     const int head = head_ok ? head_want : t.q_head0;
     const int row_base = across ? t.row0 : t.row0 + 32 * QB * qs;
     const bool split_out = it.num_splits > 1;  // fp32 partials go to the workspace
-    const bool merge_here = split_out && a.nonce != 0 && it.num_splits <= max_merge_in_tile(QW);
+    const bool merge_here = split_out && it.num_splits <= a.merge_splits;
     const int kv_begin = t.kv_begin, kv_end = t.kv_end;
     const int nstages = (kv_end - kv_begin + STEP - 1) / STEP;
     // a whole prefill brings every position fresh: no page lookups
@@ -690,12 +699,14 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
         __syncthreads();
         float* mbuf = reinterpret_cast<float*>(smem) + (size_t)qs * KW * MERGE_REGS * 64;
         float* mine = mbuf + (size_t)ks * MERGE_REGS * 64;
+        if (computes) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mine[(mb * 16 + i) * 64 + lane] = o[0][mb][i];
-        mine[(MB * 16) * 64 + lane] = m_used[0];
-        mine[(MB * 16 + 1) * 64 + lane] = l_run[0];
+                for (int i = 0; i < 16; ++i) mine[(mb * 16 + i) * 64 + lane] = o[0][mb][i];
+            mine[(MB * 16) * 64 + lane] = m_used[0];
+            mine[(MB * 16 + 1) * 64 + lane] = l_run[0];
+        }
         __syncthreads();
         float m_tot = -INFINITY;
 #pragma unroll
@@ -790,10 +801,10 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
             const bool all = __builtin_amdgcn_ballot_w64(there) == ~0ull;
             if (all && lane < it.num_splits)
                 __hip_atomic_store(marks + lane, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (lane == 0) merging = all;
+            if (lane == 0) shared.merging = all;
         }
         __syncthreads();
-        if (!merging) return;
+        if (!shared.merging) return;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const int r0 = row_base + 32 * qb, nb = min(32, it.n - r0);
@@ -865,6 +876,7 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
                 const int dim = (mb0 + mb) * 32 + 8 * q4 + 4 * hh;
                 const bf16x4 v = {(__bf16)o[qb][mb][4 * q4], (__bf16)o[qb][mb][4 * q4 + 1],
                                   (__bf16)o[qb][mb][4 * q4 + 2], (__bf16)o[qb][mb][4 * q4 + 3]};
+                if (ESTAGE && !computes) continue;
                 if (ESTAGE) *(LDS u32x2*)(ebuf + (32 * qb + qn) * EROW + dim * 2) = __builtin_bit_cast(u32x2, v);
                 else if (stored) *(u32x2*)(op + dim) = __builtin_bit_cast(u32x2, v);
             }
@@ -888,6 +900,63 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
                 }
             }
         }
+    }
+}
+
+template <int D, int QW, int KW, int QB, int NB, int NSTAGE, bool HEADS_ACROSS>
+__global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_kernel(AttnArgs a) {
+    __shared__ TileShared<2 * NSTAGE * 32 * NB * KW * D * 2> shared;
+    const TileRec t = a.tiles[blockIdx.x];
+    attn_tile<D, QW, KW, QB, NB, NSTAGE, HEADS_ACROSS, 0>(a, t, a.items[t.item], shared);
+}
+
+// Prefill-shaped tiles and the block decodes of one query head per KV head
+// (which no prefill-shaped tile takes) in one launch: the former are bound by
+// the matrix cores and the latter by HBM, so they run beside each other, one
+// of each per CU as far as they last. Both are four waves with 64-key stages;
+// two waves of a decode only stage. Prefill tiles of 256 rows are taken as
+// two of 128, whose LDS leaves room for the other kind.
+// Order: `round` prefill tiles (one per CU), as many decodes, then groups of
+// eight blocks (one per XCD) of either kind in the ratio of what is left.
+// Measured on 16 block decodes beside prefills of 1819 and 1201 rows, 32/32
+// heads: 229 us in two launches (110 + 118), 194 us in this one; all prefill
+// tiles first 206, all decodes first 212, no first round 197.
+struct MixedArgs {
+    AttnArgs a;                   // tiles: the prefill-shaped ones
+    const TileRec* decode_tiles;
+    int32_t decode_merge_splits;  // merge_splits of the decodes
+    int32_t n_prefill;            // blocks of prefill tiles (halves, when halved)
+    int32_t n_decode;
+    int32_t halved;
+    int32_t first_prefill;        // of the first round
+    int32_t first_decode;
+    uint32_t prefill_share;       // of the later groups, in 1 / 65536
+};
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void attn_mixed_kernel(MixedArgs m) {
+    __shared__ TileShared<2 * 2 * 64 * D * 2> shared;
+    const int b = blockIdx.x, head_blocks = m.first_prefill + m.first_decode;
+    int index = b;
+    bool decode = b >= m.first_prefill;
+    if (b >= head_blocks) {
+        const uint32_t g = uint32_t(b - head_blocks) >> 3;
+        const uint32_t before = uint32_t((uint64_t(g) * m.prefill_share) >> 16);
+        decode = uint32_t((uint64_t(g + 1) * m.prefill_share) >> 16) == before;
+        index = int((decode ? g - before : before) * 8) + (b & 7) + (decode ? m.first_decode : m.first_prefill);
+    } else if (decode) {
+        index = b - m.first_prefill;
+    }
+    if (index >= (decode ? m.n_decode : m.n_prefill)) return;
+    if (decode) {
+        const TileRec t = m.decode_tiles[index];
+        m.a.merge_splits = m.decode_merge_splits;
+        attn_tile<D, 1, 2, 1, 1, 2, true, 2>(m.a, t, m.a.items[t.item], shared);
+    } else {
+        TileRec t = m.a.tiles[index >> m.halved];
+        const ItemRec it = m.a.items[t.item];
+        if (m.halved) t.row0 += 4 * kWaveRows * (index & 1);
+        if (t.row0 < it.n) attn_tile<D, 4, 1, 1, 2, 2, false, 0>(m.a, t, it, shared);
     }
 }
 
@@ -981,6 +1050,22 @@ hipError_t launch_decode(const AttnArgs& args, int n_tiles, int qw, int kw, int 
     }
     *supported = false;
     return hipSuccess;
+}
+
+// Block order of a mixed launch: fills in the counts and the share of m, for
+// n_prefill blocks of prefill tiles, and returns the number of blocks (a few
+// of which find no tile left).
+int64_t mixed_order(MixedArgs* m, int64_t n_prefill) {
+    constexpr int64_t kRound = 256;  // one per CU
+    const int64_t n_decode = m->n_decode;
+    m->n_prefill = int32_t(n_prefill);
+    m->first_prefill = int32_t(std::min(n_prefill, kRound));
+    m->first_decode = int32_t(std::min(n_decode, kRound));
+    const int64_t p = (n_prefill - m->first_prefill + 7) / 8, d = (n_decode - m->first_decode + 7) / 8;
+    m->prefill_share = p + d ? uint32_t((p * 65536 + p + d - 1) / (p + d)) : 0;
+    int64_t groups = p + d;  // the share is rounded up: prefills are done by then, decodes perhaps not
+    while (groups - ((groups * int64_t(m->prefill_share)) >> 16) < d) ++groups;
+    return m->first_prefill + m->first_decode + 8 * groups;
 }
 
 // A number no other call and no leftover memory holds: a mixed counter that
@@ -1145,11 +1230,28 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
                   h->hq,
                   h->hkv,
                   h->scale_log2,
-                  h->mark_bytes > 0 ? next_nonce() : 0};
+                  h->mark_bytes > 0 ? next_nonce() : 0,
+                  0};
+    // splits up to which the tiles merge items of more than kWaveRows rows, and block decodes
+    const int prefill_qw = h->prefill_rows / kWaveRows;
+    const int rows_in_tile = args.nonce ? max_merge_in_tile(prefill_qw) : 0;
+    const int block_in_tile = args.nonce ? max_merge_in_tile(h->n_decode_tiles > 0 ? h->decode_qw : prefill_qw) : 0;
+    args.merge_splits = rows_in_tile;
 
     // 1. attention: prefill-shaped tiles (compute-bound) first, then
     // decode-shaped tiles; both also write the fresh rows into their pages
-    if (h->n_prefill_tiles > 0) {
+    const bool mixed = h->n_prefill_tiles > 0 && h->n_decode_tiles > 0 && h->decode_qw == 1 && h->decode_kw == 2 &&
+                       int64_t(h->n_prefill_tiles) + h->n_decode_tiles < INT32_MAX / 4;  // blocks count as int32
+    if (mixed) {
+        MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), block_in_tile, 0, h->n_decode_tiles,
+                    h->prefill_rows == kWidePrefillRows, 0, 0, 0};
+        m.a.tiles = reinterpret_cast<const TileRec*>(pd + h->off_prefill_tiles);
+        const int64_t blocks = mixed_order(&m, int64_t(h->n_prefill_tiles) << m.halved);
+        const void* fn = h->d == 128 ? reinterpret_cast<const void*>(&attn_mixed_kernel<128>)
+                                     : reinterpret_cast<const void*>(&attn_mixed_kernel<64>);
+        if (hipError_t e = launch(fn, dim3(unsigned(blocks)), 256u, m, stream, evs(0)); e != hipSuccess)
+            return hip_fail(e, "mixed attention launch");
+    } else if (h->n_prefill_tiles > 0) {
         args.tiles = reinterpret_cast<const TileRec*>(pd + h->off_prefill_tiles);
         hipError_t e;
         if (h->prefill_rows == kWidePrefillRows && h->d == 128)
@@ -1166,7 +1268,8 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
     } else if (hipError_t e = mark_empty(0); e != hipSuccess) {
         return hip_fail(e, "event record");
     }
-    if (h->n_decode_tiles > 0) {
+    if (!mixed && h->n_decode_tiles > 0) {
+        args.merge_splits = block_in_tile;
         args.tiles = reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles);
         bool ok = false;
         hipError_t e = h->d == 128 ? launch_decode<128>(args, h->n_decode_tiles, h->decode_qw, h->decode_kw,
@@ -1183,9 +1286,6 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
     }
 
     // 2. merge split contexts, those of the items that the tiles do not merge
-    const int prefill_qw = h->prefill_rows / kWaveRows;
-    const int rows_in_tile = args.nonce ? max_merge_in_tile(prefill_qw) : 0;
-    const int block_in_tile = args.nonce ? max_merge_in_tile(h->n_decode_tiles > 0 ? h->decode_qw : prefill_qw) : 0;
     if (h->n_merge_rows > 0 && h->max_splits > std::min(rows_in_tile, block_in_tile)) {
         MergeArgs m{reinterpret_cast<const MergeRow*>(pd + h->off_merge),
                     items,
