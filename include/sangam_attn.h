@@ -105,7 +105,10 @@ sangam_status sangam_attn_plan(const sangam_attn_desc *desc, void *plan_buf, siz
                                size_t *used);
 
 /* Device workspace bytes the forward needs for split-KV partial results
- * (fp32 O and LSE); 0 when no item is split. Returns 0 for an invalid plan. */
+ * (fp32 O and LSE) and the marks by which its tiles see that all are written;
+ * 0 when no item is split. Returns 0 for an invalid plan. Nothing in the
+ * workspace has to be set before a call; calls that overlap in time need one
+ * each. */
 size_t sangam_plan_workspace_bytes(const void *plan_buf);
 
 /* Summary of a plan, for tests and tuning. */
@@ -172,7 +175,8 @@ sangam_status sangam_attn_forward(const void *plan_host, const void *plan_dev, c
  * them. The array keeps the last call's contents; nothing in it needs to
  * start at zero (each split's partials are written before they are read).
  * Errors: as sangam_attn_forward; SANGAM_ERR_BUFFER when the plan's
- * workspace (sangam_plan_workspace_bytes) exceeds the array;
+ * split partials (sangam_plan_workspace_bytes less the marks, which have
+ * room of their own) exceed the array;
  * SANGAM_ERR_INVALID_ARG when `stream` belongs to another device.
  */
 sangam_status sangam_attn_forward_noalloc(const void *plan_host, const void *plan_dev, const void *q,
@@ -182,7 +186,7 @@ sangam_status sangam_attn_forward_noalloc(const void *plan_host, const void *pla
                                           void *out, float *lse, void *stream);
 
 /* Bytes of the device array that sangam_attn_forward_noalloc uses for split
- * partials (its largest plan workspace). */
+ * partials (a plan whose workspace is no larger always fits). */
 size_t sangam_noalloc_scratch_bytes(void);
 
 /*
@@ -192,7 +196,11 @@ size_t sangam_noalloc_scratch_bytes(void);
  * [4] and [5] of the split merge (the KV write-back runs inside the two
  * attention launches). The events travel in the kernel dispatch itself, so
  * their elapsed time is the kernel's execution time, as a kernel trace
- * reports it. A launch with no work records its two events back to back.
+ * reports it. A launch with no work records its two events back to back:
+ * the split merge too where the tiles merge all items themselves, and the
+ * decode-shaped one where the work-groups of both kinds run in one launch
+ * (one query head per KV head, block decodes beside prefills), which then
+ * carries events[0] and [1].
  * events holds six entries, each a hipEvent_t the caller created (and owns)
  * or NULL for no timestamp; otherwise identical to sangam_attn_forward.
  * Errors: as sangam_attn_forward, plus SANGAM_ERR_INVALID_ARG for a NULL

@@ -24,8 +24,7 @@ constexpr int kWidePrefillRows = kWaveRows * kWidePrefillQWaves;
 constexpr int kWidePrefillMinRows = 1024;  // every prefill-shaped item at least this long
 constexpr int kKeyAlign = 64;       // split boundaries are multiples of this many keys
 constexpr int kForcedSplitLen = 8192;  // a decode context longer than this is always split
-// Longest context range of one tile that reads cached (paged) rows: the
-// kernel stages that range's page ids in LDS.
+// Longest context range of one tile that reads cached (paged) rows.
 constexpr int kMaxCachedRange = 8192;
 
 // One work item of the batch (a block decode or a whole prefill).
