@@ -73,8 +73,7 @@ struct AttnArgs {
     int32_t hq;
     int32_t hkv;
     float scale_log2;
-    uint64_t nonce;        // marks this call's split partials as written
-    int32_t merge_splits;  // splits up to which the tiles merge an item (0: merge_kernel does)
+    uint64_t nonce;  // marks this call's split partials as written (0: merge_kernel merges)
 };
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -186,20 +185,6 @@ __device__ __forceinline__ float load_agent(const float* p) {
 }
 constexpr int kBufferAgent = 16;  // sc1 in a buffer load's cache policy
 
-// Whether the last tile to finish merges an item's S partials, given the
-// query waves qw of its tiles; else merge_kernel does. The tile reads S * qw
-// partials of 16 KiB (D = 128) by itself, the launch reads all in parallel but
-// costs 4 to 8 us with its gap. Measured, launch -> in the tile: 28/4 heads
-// (qw 4) one decode in 8 splits 18.2 -> 17.8 us, 8 decodes in 4 19.8 -> 17.4
-// and in 8 29.2 -> 30.3, 4 decodes in 12 27.6 -> 30.3; whole groups (qw 7)
-// 24 decodes in 4 70 -> 63; 32/32 heads (qw 1) one decode in 12 22.3 -> 18.4
-// and in 16 27.8 -> 22.2.
-constexpr int kMaxMergeInTile = 16;
-constexpr int kMaxMergePartials = 28;
-__host__ __device__ constexpr int max_merge_in_tile(int qw) {
-    return kMaxMergePartials / qw < kMaxMergeInTile ? kMaxMergePartials / qw : kMaxMergeInTile;
-}
-
 // Waves per SIMD the register budget is sized for: two (256 registers) when a
 // wave holds one query block.
 constexpr int waves_per_simd(int qb) { return qb == 1 ? 2 : 1; }
@@ -284,7 +269,7 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     const int head = head_ok ? head_want : t.q_head0;
     const int row_base = across ? t.row0 : t.row0 + 32 * QB * qs;
     const bool split_out = it.num_splits > 1;  // fp32 partials go to the workspace
-    const bool merge_here = split_out && it.num_splits <= a.merge_splits;
+    const bool merge_here = split_out && a.nonce != 0;
     const int kv_begin = t.kv_begin, kv_end = t.kv_end;
     const int nstages = (kv_end - kv_begin + STEP - 1) / STEP;
     // a whole prefill brings every position fresh: no page lookups
@@ -924,7 +909,6 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
 struct MixedArgs {
     AttnArgs a;                   // tiles: the prefill-shaped ones
     const TileRec* decode_tiles;
-    int32_t decode_merge_splits;  // merge_splits of the decodes
     int32_t n_prefill;            // blocks of prefill tiles (halves, when halved)
     int32_t n_decode;
     int32_t halved;
@@ -950,7 +934,6 @@ __global__ __launch_bounds__(256, 2) void attn_mixed_kernel(MixedArgs m) {
     if (index >= (decode ? m.n_decode : m.n_prefill)) return;
     if (decode) {
         const TileRec t = m.decode_tiles[index];
-        m.a.merge_splits = m.decode_merge_splits;
         attn_tile<D, 1, 2, 1, 1, 2, true, 2>(m.a, t, m.a.items[t.item], shared);
     } else {
         TileRec t = m.a.tiles[index >> m.halved];
@@ -969,20 +952,15 @@ struct MergeArgs {
     float* lse;
     int32_t hq;
     int32_t d;
-    // splits up to which the tiles merge items of more than kWaveRows rows, and block decodes
-    int32_t rows_in_tile;
-    int32_t block_in_tile;
 };
 
 // grid: (merge row, 256-element slice of the row's Hq x D/4 float4 outputs);
 // one thread per float4 of one head, so that every partial of a row is
-// loaded by a different thread in parallel. Items that the tiles merge
-// themselves are left out.
+// loaded by a different thread in parallel.
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     const MergeRow mr = a.rows[blockIdx.x];
     const ItemRec it = a.items[mr.item];
     const int S = it.num_splits;
-    if (S <= (it.n > kWaveRows ? a.rows_in_tile : a.block_in_tile)) return;
     const int d4n = a.d / 4;
     const int e = blockIdx.y * 256 + threadIdx.x;
     if (e >= a.hq * d4n) return;
@@ -1230,20 +1208,13 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
                   h->hq,
                   h->hkv,
                   h->scale_log2,
-                  h->mark_bytes > 0 ? next_nonce() : 0,
-                  0};
-    // splits up to which the tiles merge items of more than kWaveRows rows, and block decodes
-    const int prefill_qw = h->prefill_rows / kWaveRows;
-    const int rows_in_tile = args.nonce ? max_merge_in_tile(prefill_qw) : 0;
-    const int block_in_tile = args.nonce ? max_merge_in_tile(h->n_decode_tiles > 0 ? h->decode_qw : prefill_qw) : 0;
-    args.merge_splits = rows_in_tile;
-
+                  h->mark_bytes > 0 ? next_nonce() : 0};
     // 1. attention: prefill-shaped tiles (compute-bound) first, then
     // decode-shaped tiles; both also write the fresh rows into their pages
     const bool mixed = h->n_prefill_tiles > 0 && h->n_decode_tiles > 0 && h->decode_qw == 1 && h->decode_kw == 2 &&
                        int64_t(h->n_prefill_tiles) + h->n_decode_tiles < INT32_MAX / 4;  // blocks count as int32
     if (mixed) {
-        MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), block_in_tile, 0, h->n_decode_tiles,
+        MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), 0, h->n_decode_tiles,
                     h->prefill_rows == kWidePrefillRows, 0, 0, 0};
         m.a.tiles = reinterpret_cast<const TileRec*>(pd + h->off_prefill_tiles);
         const int64_t blocks = mixed_order(&m, int64_t(h->n_prefill_tiles) << m.halved);
@@ -1269,7 +1240,6 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
         return hip_fail(e, "event record");
     }
     if (!mixed && h->n_decode_tiles > 0) {
-        args.merge_splits = block_in_tile;
         args.tiles = reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles);
         bool ok = false;
         hipError_t e = h->d == 128 ? launch_decode<128>(args, h->n_decode_tiles, h->decode_qw, h->decode_kw,
@@ -1285,17 +1255,15 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
         return hip_fail(e, "event record");
     }
 
-    // 2. merge split contexts, those of the items that the tiles do not merge
-    if (h->n_merge_rows > 0 && h->max_splits > std::min(rows_in_tile, block_in_tile)) {
+    // 2. merge split contexts, unless the tiles do
+    if (h->n_merge_rows > 0 && h->mark_bytes <= 0) {
         MergeArgs m{reinterpret_cast<const MergeRow*>(pd + h->off_merge),
                     items,
                     static_cast<const float*>(workspace),
                     static_cast<uint16_t*>(out),
                     lse,
                     h->hq,
-                    h->d,
-                    rows_in_tile,
-                    block_in_tile};
+                    h->d};
         const unsigned slices = unsigned((h->hq * (h->d / 4) + 255) / 256);
         hipError_t e = launch(reinterpret_cast<const void*>(&merge_kernel), dim3(unsigned(h->n_merge_rows), slices),
                               256u, m, stream, evs(2));

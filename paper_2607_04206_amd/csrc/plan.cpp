@@ -289,7 +289,8 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
     std::vector<int32_t> positions;    // rows of kItemPosList items
     std::vector<uint32_t> page_info;   // per page, when any item is kItemPosList
     if (std::find(listed.begin(), listed.end(), 1) != listed.end()) page_info.assign(total_pages, 0u);
-    int64_t ws_floats = 0, mark_floats = 0;
+    int64_t ws_floats = 0;
+    bool in_tile = true;  // the tiles merge every split item
     int n_merge = 0, n_split_items = 0, max_splits = 1;
     for (int i = 0; i < n_items; ++i) {
         ItemRec& it = items[i];
@@ -342,11 +343,24 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
             it.ws_lse = ws_floats;
             ws_floats += S * it.n * int64_t(hq);
             ws_floats = round_up(ws_floats, 64);
-            const int64_t marks = merge_mark_floats(it, hq);
-            ws_floats += marks;
-            mark_floats += marks;
+            in_tile &= S <= max_merge_in_tile(it.n <= kWaveRows && !fuse ? qw : prefill_rows / kWaveRows);
         }
     }
+    int64_t mark_floats = 0;
+    for (const ItemRec& it : items)
+        if (it.num_splits > 1) mark_floats += merge_mark_floats(it, hq);
+    // no room in the header's field: terabytes of partials
+    if (!in_tile || mark_floats * int64_t(sizeof(float)) > INT32_MAX) mark_floats = 0;
+    if (mark_floats > 0) {
+        int64_t before = 0;  // marks of the items before
+        for (ItemRec& it : items) {
+            if (it.num_splits == 1) continue;
+            it.ws_o += before;
+            it.ws_lse += before;
+            before += merge_mark_floats(it, hq);
+        }
+    }
+    ws_floats += mark_floats;
 
     // ---- tiles
     std::vector<TileRec> dec, pre;
@@ -490,9 +504,7 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
     h.prefill_rows = prefill_rows;
     h.n_fused_decode_tiles = int32_t(n_fused * hkv * fused_tiles_per_kv_head);
     h.workspace_bytes = ws_floats * int64_t(sizeof(float));
-    // 0 (no room in the field, terabytes of partials): merged by a launch
-    const int64_t marks = mark_floats * int64_t(sizeof(float));
-    h.mark_bytes = marks <= INT32_MAX ? int32_t(marks) : 0;
+    h.mark_bytes = int32_t(mark_floats * int64_t(sizeof(float)));
     h.off_items = off_items;
     h.off_decode_tiles = off_dec;
     h.off_prefill_tiles = off_pre;

@@ -112,7 +112,7 @@ struct PlanHeader {
     int32_t max_splits;
     int32_t prefill_rows;  // query rows per prefill-shaped tile: kPrefillRows or kWidePrefillRows
     int32_t n_fused_decode_tiles;
-    int32_t mark_bytes;  // of the workspace: merge marks (0 in older plans, which have none)
+    int32_t mark_bytes;  // of the workspace: merge marks (0: none, merge_kernel merges)
     int64_t workspace_bytes;
 
     uint64_t off_items;
@@ -134,6 +134,23 @@ inline int64_t merge_marks(const ItemRec& it, int hq) {
 }
 inline int64_t merge_mark_floats(const ItemRec& it, int hq) {
     return (int64_t(it.n + kWaveRows - 1) / kWaveRows * hq * it.num_splits * 2 + 63) / 64 * 64;
+}
+
+// The tile that finishes last merges an item's S partials, given the query
+// waves qw of its tiles, if no item of the plan is above this limit; else the
+// plan has no marks and merge_kernel merges all. The tile reads S * qw
+// partials of 16 KiB (D = 128) by itself, the launch reads all in parallel but
+// costs 4 to 8 us with its gap. Measured, launch -> in the tile: 28/4 heads
+// (qw 4) one decode in 8 splits 18.2 -> 17.8 us, 8 decodes in 4 19.8 -> 17.4
+// and in 8 29.2 -> 30.3, 4 decodes in 12 27.6 -> 30.3; whole groups (qw 7)
+// 24 decodes in 4 70 -> 63; 32/32 heads (qw 1) one decode in 12 22.3 -> 18.4
+// and in 16 27.8 -> 22.2. Both ways in one call add up: 4 decodes in 3 to 14
+// splits, 32/8 heads of 64, took 19.5 us with all in the launch and 21.7 us
+// with the items of up to 7 splits in their tiles.
+constexpr int kMaxMergeInTile = 16;
+constexpr int kMaxMergePartials = 28;
+constexpr int max_merge_in_tile(int qw) {
+    return kMaxMergePartials / qw < kMaxMergeInTile ? kMaxMergePartials / qw : kMaxMergeInTile;
 }
 
 static_assert(sizeof(ItemRec) == 56, "ItemRec layout is part of the blob format");

@@ -1,5 +1,6 @@
-"""Split contexts merged by the tile that finishes last (up to eight splits of
-an item) or by the merge launch (more): parity with the oracle at the edges of
+"""Split contexts merged by the tile that finishes last (up to seven splits of
+every item at four query waves a tile, up to 16 at one) or by the merge launch
+(any item above): parity with the oracle at the edges of
 both, the same bits whatever the workspace held, and graph replays, whose marks
 repeat, over a workspace that nothing clears in between."""
 import pytest
@@ -25,11 +26,12 @@ def dev():
     return torch.device("cuda:0")
 
 
-@pytest.mark.parametrize("force", [2, 8, 9])
+@pytest.mark.parametrize("force", [2, 7, 8])
 def test_marks_follow_the_partials(force):
     """Every split item's marks (8 bytes per 32 rows, head and split) sit
     after its partials, inside the workspace and apart from the next item's;
-    the header field counts them."""
+    the header field counts them. With an item of more splits than a tile
+    merges there are none."""
     wl = batch(28, 4, 128)
     p = plan_of(wl, force_kv_splits=force)
     h, items, *_ = parse(p)
@@ -38,14 +40,14 @@ def test_marks_follow_the_partials(force):
         S, n = int(it["num_splits"]), int(it["n"])
         assert int(it["ws_o"]) >= end
         at = int(it["ws_lse"]) + -(-S * n * 28 // 64) * 64
-        size = -(-(-(-n // 32) * 28 * S * 2) // 64) * 64
+        size = -(-(-(-n // 32) * 28 * S * 2) // 64) * 64 if force <= 7 else 0
         end, marks = at + size, marks + size
     assert int(h["reserved"]) == 4 * marks and end * 4 == p.workspace_bytes
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 64), (4, 4, 128), (28, 4, 128), (8, 4, 64), (16, 1, 128)])
-@pytest.mark.parametrize("force", [2, 8, 9])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 64), (4, 4, 128), (4, 2, 128), (28, 4, 128), (8, 4, 64), (16, 1, 128)])
+@pytest.mark.parametrize("force", [2, 7, 8, 14, 16, 17])
 def test_merged_rows(dev, hq, hkv, d, force):
     from paper_2607_04206_amd import attn
     wl = batch(hq, hkv, d)
