@@ -26,6 +26,7 @@
 // A small decode-only batch of such groups takes the same tiles, with its
 // contexts cut to fill the CUs.
 #include <algorithm>
+#include <functional>
 #include <cstring>
 #include <numeric>
 #include <string>
@@ -78,6 +79,10 @@ static int decode_kv_waves(int qw) {
 static int64_t min_chunk(int /*qw*/) { return 2048; }
 // the same floor while a decode launch leaves CUs idle (see below)
 static int64_t min_chunk_idle(int qw) { return qw == 1 ? 256 : 512; }
+
+// What a whole-group decode tile costs beside its stages, in 64-key stages (of
+// about 2.2 us at 28/4 heads): start-up and epilogue, partials, a merge launch.
+constexpr int64_t kTileStages = 3, kSplitStages = 2, kMergeStages = 3;
 
 // XCDs of the chip (each with its own L2), and the rounds of tiles per
 // work-group slot from which a prefill-shaped launch takes the XCD-aware order
@@ -282,6 +287,44 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
                 else hi = mid;
             }
             chunk = hi;
+        }
+        // With nearly as many contexts as slots that chunk leaves a long
+        // context whole among short ones, and the launch lasts as long as it.
+        // Group tiles of three waves or more fill a CU by themselves, so
+        // their time adds up per CU: shorter chunks are taken if dealing
+        // them out longest first ends a tenth sooner. Measured: 63 decodes of
+        // up to 3599 keys, 28/4 heads, 79.8 -> 51.4 us (252 -> 312 tiles); 31 of
+        // up to 4352, 32/8 heads, 92.9 -> 70.1 us; 20 and 48 decodes keep
+        // their chunks. The simulation costs the host a few us.
+        if (qw >= 3) {
+            const int64_t cus = std::max<int64_t>(slots / (int64_t(hkv) * tiles_per_kv_head), 1);
+            int64_t best = 0, taken = chunk;
+            std::vector<int64_t> costs, busy;
+            for (int64_t c = chunk; c >= min_chunk_idle(qw); c = round_up(c * 3 / 4, kKeyAlign) < c ? round_up(c * 3 / 4, kKeyAlign) : 0) {
+                costs.clear();
+                bool in_tile = true;
+                for (int i = 0; i < n_items; ++i) {
+                    const int64_t L = d->kv_len[i], S = ceil_div(L, c);
+                    if (int64_t(d->q_indptr[i + 1]) - d->q_indptr[i] > kWaveRows) continue;
+                    in_tile &= S <= max_merge_in_tile(qw);
+                    // in stages: its own, the start and the end of a tile, writing and merging partials
+                    const int64_t cost = ceil_div(ceil_div(L, S), kKeyAlign) + kTileStages + (S > 1 ? kSplitStages : 0);
+                    costs.insert(costs.end(), size_t(S), cost);
+                }
+                std::sort(costs.begin(), costs.end(), std::greater<int64_t>());
+                busy.assign(size_t(cus), 0);  // a heap, the first to be free on top
+                for (const int64_t cost : costs) {
+                    std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+                    busy.back() += cost;
+                    std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+                }
+                const int64_t end = *std::max_element(busy.begin(), busy.end()) + (in_tile ? 0 : kMergeStages);
+                if (best == 0 || 10 * end < 9 * best) {
+                    best = end;
+                    taken = c;
+                }
+            }
+            chunk = taken;
         }
     }
 
