@@ -1079,7 +1079,6 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // for the symbol: kernels receive the device address that hipGetSymbolAddress
 // returns for the current device, cached per device below.
 namespace {
-constexpr size_t kScratchBytes = size_t(32) << 20;  // partials it holds
 // beside them the merge marks of any plan with that many bytes of partials
 // (at worst 256 bytes of marks to 768 of partials: two splits of one row)
 constexpr size_t kScratchMarks = kScratchBytes / 3 + 4096;

@@ -303,14 +303,19 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
             for (int64_t c = chunk; c >= min_chunk_idle(qw); c = round_up(c * 3 / 4, kKeyAlign) < c ? round_up(c * 3 / 4, kKeyAlign) : 0) {
                 costs.clear();
                 bool in_tile = true;
+                int64_t partials = 0;  // floats, rounded up
                 for (int i = 0; i < n_items; ++i) {
                     const int64_t L = d->kv_len[i], S = ceil_div(L, c);
-                    if (int64_t(d->q_indptr[i + 1]) - d->q_indptr[i] > kWaveRows) continue;
+                    const int64_t n = int64_t(d->q_indptr[i + 1]) - d->q_indptr[i];
+                    if (n > kWaveRows) continue;
+                    if (S > 1) partials += S * n * hq * (D + 1) + 128;
                     in_tile &= S <= max_merge_in_tile(qw);
                     // in stages: its own, the start and the end of a tile, writing and merging partials
                     const int64_t cost = ceil_div(ceil_div(L, S), kKeyAlign) + kTileStages + (S > 1 ? kSplitStages : 0);
                     costs.insert(costs.end(), size_t(S), cost);
                 }
+                // the allocation-free forward has to take what it took unsplit
+                if (best > 0 && partials * int64_t(sizeof(float)) > int64_t(kScratchBytes)) break;
                 std::sort(costs.begin(), costs.end(), std::greater<int64_t>());
                 busy.assign(size_t(cus), 0);  // a heap, the first to be free on top
                 for (const int64_t cost : costs) {

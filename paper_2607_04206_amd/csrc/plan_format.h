@@ -123,6 +123,9 @@ struct PlanHeader {
     uint64_t off_page_info;  // uint32 per page (page_indptr order), when any item is kItemPosList
 };
 
+// Split partials that the allocation-free forward holds.
+constexpr size_t kScratchBytes = size_t(32) << 20;
+
 // Merge marks of a split item: per 32-row block, query head and split one
 // uint64 (a tile uses those of its first block and head), after the item's
 // partial LSE in the workspace. Float offset, and their number of floats.

@@ -28,6 +28,22 @@ def test_long_context_is_cut(hq, hkv, d, count, long, cut):
     assert (lens >= items["L"]).all()
 
 
+def test_cut_stays_within_the_scratch():
+    """Contexts of which many gain by a cut: never more partials than the
+    allocation-free forward holds."""
+    from paper_2607_04206_amd._lib import lib
+    rng = np.random.default_rng(3)
+    for _ in range(60):
+        count = int(rng.integers(20, 32))
+        lens = np.exp(rng.normal(np.log(3000), 1.0, count)).astype(int) + 600
+        wl = workloads.make_workload("plan_scratch", 5, hq=64, hkv=8, d=128, prefills=[],
+                                     decodes=[(64, int(min(n, 7000))) for n in lens])
+        p = plan_of(wl)
+        h, items, *_ = parse(p)
+        assert len(items) == count
+        assert p.workspace_bytes - int(h["reserved"]) <= int(lib.sangam_noalloc_scratch_bytes()) or p.info.num_decode_tiles <= 256
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("hq,hkv,d,count", [(28, 4, 128, 63), (6, 2, 64, 127)])
 def test_cut_batch_matches(hq, hkv, d, count):
