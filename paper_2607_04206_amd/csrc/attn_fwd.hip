@@ -693,24 +693,28 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
             mine[(MB * 16 + 1) * 64 + lane] = l_run[0];
         }
         __syncthreads();
-        float m_tot = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < KW; ++k) m_tot = fmaxf(m_tot, mbuf[(size_t)(k * MERGE_REGS + MB * 16) * 64 + lane]);
+        static_assert(KW == 2, "sums of two");
+        const float* src[2] = {mbuf, mbuf + MERGE_REGS * 64};
+        const float m_tot = fmaxf(src[0][(MB * 16) * 64 + lane], src[1][(MB * 16) * 64 + lane]);
         // wave ks = 0 always holds a valid key, so m_tot is finite
-        l_run[0] = 0.0f;
+        float sc[2], l[2];
 #pragma unroll
-        for (int k = 0; k < KW; ++k) {
-            const float* src = mbuf + (size_t)k * MERGE_REGS * 64;
-            const float sck = __builtin_amdgcn_exp2f(src[(MB * 16) * 64 + lane] - m_tot);
-            l_run[0] = k == 0 ? sck * src[(MB * 16 + 1) * 64 + lane] : l_run[0] + sck * src[(MB * 16 + 1) * 64 + lane];
-#pragma unroll
-            for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float v = sck * src[((mb0 + mb) * 16 + i) * 64 + lane];
-                    o[0][mb][i] = k == 0 ? v : o[0][mb][i] + v;
-                }
+        for (int k = 0; k < 2; ++k) {
+            sc[k] = __builtin_amdgcn_exp2f(src[k][(MB * 16) * 64 + lane] - m_tot);
+            l[k] = src[k][(MB * 16 + 1) * 64 + lane];
         }
+        // Which product of a sum is fused is written out: the compiler may
+        // take either, and another build would differ in the last bits.
+        const float l1 = sc[1] * l[1];
+        l_run[0] = __builtin_fmaf(sc[0], l[0], l1);
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int at = ((mb0 + mb) * 16 + i) * 64 + lane;
+                const float o0 = sc[0] * src[0][at];
+                o[0][mb][i] = __builtin_fmaf(sc[1], src[1][at], o0);
+            }
         m_used[0] = m_tot;
     }
 
