@@ -207,7 +207,9 @@ struct TileShared {
 //   QB     32-row query blocks per wave: every K and V fragment read from
 //          LDS feeds QB MFMAs, so QB = 2 halves LDS traffic per flop
 //   NB     32-key blocks per wave per stage
-//   NSTAGE K/V stage buffers in LDS (NSTAGE - 1 stages in flight)
+//   NSTAGE K/V stage buffers in LDS (NSTAGE - 1 stages in flight). 1: K and V
+//          have one buffer each, and K of the next stage arrives while V of
+//          this one is used, V while its K is
 //   HELP   more waves, which only stage and write back
 template <int D, int QW, int KW, int QB, int NB, int NSTAGE, bool HEADS_ACROSS, int HELP, typename Shared>
 __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, const ItemRec it, Shared& shared) {
@@ -237,12 +239,14 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     static_assert(KW == 1 || (QW * KW * MERGE_REGS * 64 * 4) <= 2 * NSTAGE * TILE,
                   "cross-wave merge must fit in the stage buffers");
     static_assert(MB % KW == 0, "the waves of a query slot share its dims");
-    static_assert(NSTAGE >= 2 && NSTAGE <= 4, "2 to 4 stage buffers");
+    static_assert(NSTAGE >= 1 && NSTAGE <= 4, "1 to 4 stage buffers");
+    constexpr bool TURNS = NSTAGE == 1;  // K and V take turns
+    static_assert(!TURNS || (KW == 1 && !HEADS_ACROSS && HELP == 0), "every wave meets the barrier between K and V");
     // pages a tile's write-back can touch: its rows at any offset, or one per listed row
     static_assert((32 * QB * QW + 15) / 16 + 1 <= kWaveRows && kWaveRows <= NT, "one thread per write-back page id");
     // with more than two buffers the wait counts loads, so every wave must
     // issue the same number per stage
-    static_assert(NSTAGE == 2 || SP % NW == 0, "deeper pipelines need whole staging rounds");
+    static_assert(NSTAGE <= 2 || SP % NW == 0, "deeper pipelines need whole staging rounds");
     static_assert(64 % SP == 0 && (NSTAGE - 1) * SP < 64, "a stage's page ids sit in one register of 64 lanes");
 
     static_assert(sizeof(shared.stages) >= 2 * NSTAGE * TILE, "the stage buffers");
@@ -263,7 +267,7 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     // cut into a prefill-shaped one (whose last tile of a GQA group may hold
     // fewer heads than waves: the extra waves only stage K/V, write back and
     // meet the barriers; they compute and store nothing)
-    const bool across = HEADS_ACROSS || (t.flags & kTileHeadsAcross);
+    const bool across = HEADS_ACROSS || (!TURNS && (t.flags & kTileHeadsAcross));
     const int head_want = across ? t.q_head0 + qs : t.q_head0;
     const bool head_ok = computes && head_want < (t.kv_head + 1) * (a.hq / a.hkv);
     const int head = head_ok ? head_want : t.q_head0;
@@ -344,7 +348,8 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     const uint16_t* vfresh_w = vfresh + (int64_t)(kv_begin + wave * 16) * (int64_t)row_stride;
     const size_t stage_stride = STEP * row_stride;  // elements
 
-    auto issue_stage = [&](int st, int buf) __attribute__((always_inline)) {
+    // do_k, do_v: whether to copy the stage's K rows and its V rows
+    auto issue_stage = [&](int st, int buf, auto do_k, auto do_v) __attribute__((always_inline)) {
         uint8_t* kb = smem + buf * 2 * TILE;
         uint8_t* vb = kb + TILE;
         const int pl0 = st * SP & 63;  // lane holding the id of the stage's first page
@@ -359,12 +364,12 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
                 LDS void* kd = (LDS void*)(kb + k * 16 * ROWB);
                 LDS void* vd = (LDS void*)(vb + k * 16 * ROWB);
                 if (all_fresh) {
-                    copy_page(kf + i * NW * 16 * row_stride, foff_k, kd);
-                    copy_page(vf + i * NW * 16 * row_stride, foff_v, vd);
+                    if (do_k) copy_page(kf + i * NW * 16 * row_stride, foff_k, kd);
+                    if (do_v) copy_page(vf + i * NW * 16 * row_stride, foff_v, vd);
                 } else {
                     const size_t off = size_t(uint32_t(__builtin_amdgcn_readlane(pv, pl0 + k))) * page_stride;
-                    copy_page(kcache + off, coff_k, kd);
-                    copy_page(vcache + off, coff_v, vd);
+                    if (do_k) copy_page(kcache + off, coff_k, kd);
+                    if (do_v) copy_page(vcache + off, coff_v, vd);
                 }
             }
             return;
@@ -381,8 +386,8 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
             const size_t off = all_fresh ? 0 : (size_t)__builtin_amdgcn_readlane(pv, pl) * page_stride;
             if (key0 + 16 <= kv_end && !all_fresh &&
                 (plist ? (inf & 0xFFFFu) == 0 : key0 + 16 <= it.o || key0 >= it.o + it.n)) {
-                copy_page(kcache + off, coff_k, kd);
-                copy_page(vcache + off, coff_v, vd);
+                if (do_k) copy_page(kcache + off, coff_k, kd);
+                if (do_v) copy_page(vcache + off, coff_v, vd);
                 continue;
             }
             // fresh rows of a block, listed positions, the range's partial
@@ -405,8 +410,8 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
                 ak[j] = (fresh ? fk : (uint64_t)(kcache + off)) + uint64_t(lo + ((pos ^ swz_k<D>(r)) << 4));
                 av[j] = (fresh ? fv : (uint64_t)(vcache + off)) + uint64_t(lo + ((pos ^ swz_v<D>(r)) << 4));
             }
-            copy_page(ak, kd);
-            copy_page(av, vd);
+            if (do_k) copy_page(ak, kd);
+            if (do_v) copy_page(av, vd);
         }
     };
 
@@ -431,7 +436,7 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     const int wpg0 = wb_lo >> 4;
     const int wst0 = writer ? (wb_lo - kv_begin) / STEP : nstages;  // stages [wst0, wst1) hold such rows
     const int wst1 = writer ? (wb_hi - 1 - kv_begin) / STEP + 1 : 0;
-    auto write_back = [&](int st) {
+    auto write_back = [&](int st, auto do_k, auto do_v) {
         const int key0 = kv_begin + st * STEP;
         const int lo = max(wb_lo, key0), hi = min(wb_hi, key0 + STEP);
         if (lo >= hi) return;
@@ -446,8 +451,8 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
                 const u32x4 kv = *(const LDS u32x4*)(kb + r * ROWB + ((pos ^ swz_k<D>(r)) << 4));
                 const u32x4 vv = *(const LDS u32x4*)(vb + r * ROWB + ((pos ^ swz_v<D>(r)) << 4));
                 const size_t dst = (((size_t)wpages[row] * a.hkv + t.kv_head) * 16 + (p & 15)) * D + pos * 8;
-                *(u32x4*)(a.k_cache + dst) = kv;
-                *(u32x4*)(a.v_cache + dst) = vv;
+                if (do_k) *(u32x4*)(a.k_cache + dst) = kv;
+                if (do_v) *(u32x4*)(a.v_cache + dst) = vv;
             }
             return;
         }
@@ -457,8 +462,8 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
             const u32x4 kv = *(const LDS u32x4*)(kb + r * ROWB + ((pos ^ swz_k<D>(r)) << 4));
             const u32x4 vv = *(const LDS u32x4*)(vb + r * ROWB + ((pos ^ swz_v<D>(r)) << 4));
             const size_t dst = (((size_t)wpages[(p >> 4) - wpg0] * a.hkv + t.kv_head) * 16 + (p & 15)) * D + pos * 8;
-            *(u32x4*)(a.k_cache + dst) = kv;
-            *(u32x4*)(a.v_cache + dst) = vv;
+            if (do_k) *(u32x4*)(a.k_cache + dst) = kv;
+            if (do_v) *(u32x4*)(a.v_cache + dst) = vv;
         }
     };
 
@@ -506,7 +511,8 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     // 1.30 -> 1.16 us at D = 128, 1.07 -> 0.85 us at D = 64; two: 1.98 -> 1.96
     // us and 1.32 -> 1.24 us (at D = 128 two work-groups draw the power limit:
     // the same MFMAs on random operands without the rest take 1.33 us).
-    auto attend = [&](int st, auto tail) __attribute__((always_inline)) {
+    // between: called when the wave is done with the stage's K and is to read its V
+    auto attend = [&](int st, auto tail, auto between) __attribute__((always_inline)) {
         constexpr bool TAIL = decltype(tail)::value;
         constexpr int NK = NB * DS;      // K fragments (and QK^T steps)
         constexpr int NV = NB * 2 * MB;  // V fragments (and PV steps)
@@ -552,7 +558,7 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
                     for (int i = 0; i < 16; ++i) s[qb][b][i] = 0.0f;
                 s[qb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[n % RA], qf[qb][k], s[qb][b], 0, 0, 0);
             }
-            frag[n % RA] = read_frag(n + RA);
+            if (!TURNS || n + RA < NK) frag[n % RA] = read_frag(n + RA);
             // the previous block's scores are written two steps into this one
             if (b > 0 && k >= 2) take_max(b - 1, (k - 2) * 16 / (DS - 2), (k - 1) * 16 / (DS - 2));
             __builtin_amdgcn_sched_barrier(0);
@@ -581,6 +587,13 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
 #pragma unroll
                     for (int i = 0; i < 16; ++i) o[qb][mb][i] *= alpha;
             }
+        }
+
+        if constexpr (TURNS) {
+            between();
+#pragma unroll
+            for (int n = NK; n < NK + RA; ++n) frag[n % RA] = read_frag(n);
+            __builtin_amdgcn_sched_barrier(0);
         }
 
         // P = exp2(s c - m) rounded to bf16 (the PV operand); l += the rounded
@@ -652,28 +665,51 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     const int nwp = writer ? plist ? it.n : ((wb_hi + 15) >> 4) - wpg0 : 0;
     int32_t wpage = 0;
     if (tid < nwp) wpage = a.page_ids[it.page_start + (plist ? lpos >> 4 : wpg0 + tid)];
-    for (int k = 0; k < NSTAGE - 1 && k < nstages; ++k) issue_stage(k, k);
-    if (NSTAGE == 2) wait_q();
+    constexpr auto yes = std::true_type{};
+    constexpr auto no = std::false_type{};
+    for (int k = 0; k < NSTAGE - 1 && k < nstages; ++k) issue_stage(k, k, yes, yes);
+    if (TURNS) issue_stage(0, 0, yes, no);
+    if (NSTAGE <= 2) wait_q();
     if (tid < nwp) {
         wpages[tid] = wpage;
         if (plist) fpos[tid] = lpos;
     }
     int st = 0;
-    for (; st < full_stages; ++st) {
-        wait_stage(st);
-        __syncthreads();
-        if (st + NSTAGE - 1 < nstages) {
-            issue_stage(st + NSTAGE - 1, (st + NSTAGE - 1) % NSTAGE);
-            next_pages(st + NSTAGE - 1);
+    if constexpr (TURNS) {
+        // a stage: its K is there, V on its way under QK^T, the next K under PV
+        auto stage = [&](auto tail) __attribute__((always_inline)) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            issue_stage(st, 0, no, yes);
+            next_pages(st);
+            if (st >= wst0 && st < wst1) write_back(st, yes, no);
+            attend(st, tail, [&]() __attribute__((always_inline)) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (st + 1 < nstages) issue_stage(st + 1, 0, yes, no);
+                if (st >= wst0 && st < wst1) write_back(st, no, yes);
+            });
+        };
+        for (; st < full_stages; ++st) stage(std::false_type{});
+        if (st < nstages) stage(std::true_type{});
+    } else {
+        auto go_on = []() {};
+        for (; st < full_stages; ++st) {
+            wait_stage(st);
+            __syncthreads();
+            if (st + NSTAGE - 1 < nstages) {
+                issue_stage(st + NSTAGE - 1, (st + NSTAGE - 1) % NSTAGE, yes, yes);
+                next_pages(st + NSTAGE - 1);
+            }
+            if (st >= wst0 && st < wst1) write_back(st, yes, yes);
+            if (head_ok) attend(st, std::false_type{}, go_on);  // a wave past its tile's GQA group only stages and writes back
         }
-        if (st >= wst0 && st < wst1) write_back(st);
-        if (head_ok) attend(st, std::false_type{});  // a wave past its tile's GQA group only stages and writes back
-    }
-    if (st < nstages) {  // the last, partial stage
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (st >= wst0 && st < wst1) write_back(st);
-        if (head_ok) attend(st, std::true_type{});
+        if (st < nstages) {  // the last, partial stage
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (st >= wst0 && st < wst1) write_back(st, yes, yes);
+            if (head_ok) attend(st, std::true_type{}, go_on);
+        }
     }
 
     // ---- combine the context sub-ranges of the waves that share query rows:
@@ -902,9 +938,12 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
 // Prefill-shaped tiles and the block decodes of one query head per KV head
 // (which no prefill-shaped tile takes) in one launch: the former are bound by
 // the matrix cores and the latter by HBM, so they run beside each other, one
-// of each per CU as far as they last. Both are four waves with 64-key stages;
-// two waves of a decode only stage. Prefill tiles of 256 rows are taken as
-// two of 128, whose LDS leaves room for the other kind.
+// of each per CU as far as they last. Both are four waves and hold 64 KiB of
+// LDS; two waves of a decode only stage. Prefill tiles of 256 rows (WIDE) are
+// taken as two of 128 that keep their 128-key stages, so that a prefill's sums
+// are those of a launch without decodes, bit for bit: K and V have one buffer
+// each and take turns (with two of 64 keys each, 16 decodes beside 1819 and
+// 1201 rows take 175 us instead of 180, but the sums differ by 2e-3).
 // Order: `round` prefill tiles (one per CU), as many decodes, then groups of
 // eight blocks (one per XCD) of either kind in the ratio of what is left.
 // Measured on 16 block decodes beside prefills of 1819 and 1201 rows, 32/32
@@ -915,13 +954,12 @@ struct MixedArgs {
     const TileRec* decode_tiles;
     int32_t n_prefill;            // blocks of prefill tiles (halves, when halved)
     int32_t n_decode;
-    int32_t halved;
     int32_t first_prefill;        // of the first round
     int32_t first_decode;
     uint32_t prefill_share;       // of the later groups, in 1 / 65536
 };
 
-template <int D>
+template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 2) void attn_mixed_kernel(MixedArgs m) {
     __shared__ TileShared<2 * 2 * 64 * D * 2> shared;
     const int b = blockIdx.x, head_blocks = m.first_prefill + m.first_decode;
@@ -940,10 +978,10 @@ __global__ __launch_bounds__(256, 2) void attn_mixed_kernel(MixedArgs m) {
         const TileRec t = m.decode_tiles[index];
         attn_tile<D, 1, 2, 1, 1, 2, true, 2>(m.a, t, m.a.items[t.item], shared);
     } else {
-        TileRec t = m.a.tiles[index >> m.halved];
+        TileRec t = m.a.tiles[WIDE ? index >> 1 : index];
         const ItemRec it = m.a.items[t.item];
-        if (m.halved) t.row0 += 4 * kWaveRows * (index & 1);
-        if (t.row0 < it.n) attn_tile<D, 4, 1, 1, 2, 2, false, 0>(m.a, t, it, shared);
+        if (WIDE) t.row0 += 4 * kWaveRows * (index & 1);
+        if (t.row0 < it.n) attn_tile<D, 4, 1, 1, WIDE ? 4 : 2, WIDE ? 1 : 2, false, 0>(m.a, t, it, shared);
     }
 }
 
@@ -1217,12 +1255,13 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
     const bool mixed = h->n_prefill_tiles > 0 && h->n_decode_tiles > 0 && h->decode_qw == 1 && h->decode_kw == 2 &&
                        int64_t(h->n_prefill_tiles) + h->n_decode_tiles < INT32_MAX / 4;  // blocks count as int32
     if (mixed) {
-        MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), 0, h->n_decode_tiles,
-                    h->prefill_rows == kWidePrefillRows, 0, 0, 0};
+        const bool wide = h->prefill_rows == kWidePrefillRows;
+        MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), 0, h->n_decode_tiles, 0, 0, 0};
         m.a.tiles = reinterpret_cast<const TileRec*>(pd + h->off_prefill_tiles);
-        const int64_t blocks = mixed_order(&m, int64_t(h->n_prefill_tiles) << m.halved);
-        const void* fn = h->d == 128 ? reinterpret_cast<const void*>(&attn_mixed_kernel<128>)
-                                     : reinterpret_cast<const void*>(&attn_mixed_kernel<64>);
+        const int64_t blocks = mixed_order(&m, int64_t(h->n_prefill_tiles) << int(wide));
+        const void* fn = h->d == 64 ? reinterpret_cast<const void*>(&attn_mixed_kernel<64, false>)
+                         : wide     ? reinterpret_cast<const void*>(&attn_mixed_kernel<128, true>)
+                                    : reinterpret_cast<const void*>(&attn_mixed_kernel<128, false>);
         if (hipError_t e = launch(fn, dim3(unsigned(blocks)), 256u, m, stream, evs(0)); e != hipSuccess)
             return hip_fail(e, "mixed attention launch");
     } else if (h->n_prefill_tiles > 0) {
