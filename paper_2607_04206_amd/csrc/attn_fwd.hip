@@ -27,7 +27,6 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <random>
@@ -35,6 +34,7 @@
 #include <type_traits>
 
 #include "../../include/sangam_attn.h"
+#include "mixed_order.h"
 #include "plan_format.h"
 
 namespace sangam {
@@ -952,37 +952,23 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
 struct MixedArgs {
     AttnArgs a;                   // tiles: the prefill-shaped ones
     const TileRec* decode_tiles;
-    int32_t n_prefill;            // blocks of prefill tiles (halves, when halved)
-    int32_t n_decode;
-    int32_t first_prefill;        // of the first round
-    int32_t first_decode;
-    uint32_t prefill_share;       // of the later groups, in 1 / 65536
+    MixedOrder order;
 };
 
 template <int D, bool WIDE>
 __global__ __launch_bounds__(256, 2) void attn_mixed_kernel(MixedArgs m) {
     __shared__ TileShared<2 * 2 * 64 * D * 2> shared;
-    const int b = blockIdx.x, head_blocks = m.first_prefill + m.first_decode;
-    int index = b;
-    bool decode = b >= m.first_prefill;
-    if (b >= head_blocks) {
-        const uint32_t g = uint32_t(b - head_blocks) >> 3;
-        const uint32_t before = uint32_t((uint64_t(g) * m.prefill_share) >> 16);
-        decode = uint32_t((uint64_t(g + 1) * m.prefill_share) >> 16) == before;
-        index = int((decode ? g - before : before) * 8) + (b & 7) + (decode ? m.first_decode : m.first_prefill);
-    } else if (decode) {
-        index = b - m.first_prefill;
-    }
-    if (index >= (decode ? m.n_decode : m.n_prefill)) return;
-    if (decode) {
-        const TileRec t = m.decode_tiles[index];
+    const MixedBlock b = mixed_block(m.order, blockIdx.x);
+    if (b.index < 0) return;
+    if (b.decode) {
+        const TileRec t = m.decode_tiles[b.index];
         attn_tile<D, 1, 2, 1, 1, 2, true, 2>(m.a, t, m.a.items[t.item], shared);
-    } else {
-        TileRec t = m.a.tiles[WIDE ? index >> 1 : index];
-        const ItemRec it = m.a.items[t.item];
-        if (WIDE) t.row0 += 4 * kWaveRows * (index & 1);
-        if (t.row0 < it.n) attn_tile<D, 4, 1, 1, WIDE ? 4 : 2, WIDE ? 1 : 2, false, 0>(m.a, t, it, shared);
+        return;
     }
+    TileRec t = m.a.tiles[WIDE ? b.index >> 1 : b.index];
+    const ItemRec it = m.a.items[t.item];
+    if (WIDE) t.row0 += kPrefillRows * (b.index & 1);
+    if (t.row0 < it.n) attn_tile<D, 4, 1, 1, WIDE ? 4 : 2, WIDE ? 1 : 2, false, 0>(m.a, t, it, shared);
 }
 
 // --------------------------------------------------------------- split merge
@@ -1070,22 +1056,6 @@ hipError_t launch_decode(const AttnArgs& args, int n_tiles, int qw, int kw, int 
     }
     *supported = false;
     return hipSuccess;
-}
-
-// Block order of a mixed launch: fills in the counts and the share of m, for
-// n_prefill blocks of prefill tiles, and returns the number of blocks (a few
-// of which find no tile left).
-int64_t mixed_order(MixedArgs* m, int64_t n_prefill) {
-    constexpr int64_t kRound = 256;  // one per CU
-    const int64_t n_decode = m->n_decode;
-    m->n_prefill = int32_t(n_prefill);
-    m->first_prefill = int32_t(std::min(n_prefill, kRound));
-    m->first_decode = int32_t(std::min(n_decode, kRound));
-    const int64_t p = (n_prefill - m->first_prefill + 7) / 8, d = (n_decode - m->first_decode + 7) / 8;
-    m->prefill_share = p + d ? uint32_t((p * 65536 + p + d - 1) / (p + d)) : 0;
-    int64_t groups = p + d;  // the share is rounded up: prefills are done by then, decodes perhaps not
-    while (groups - ((groups * int64_t(m->prefill_share)) >> 16) < d) ++groups;
-    return m->first_prefill + m->first_decode + 8 * groups;
 }
 
 // A number no other call and no leftover memory holds: a mixed counter that
@@ -1256,9 +1226,10 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
                        int64_t(h->n_prefill_tiles) + h->n_decode_tiles < INT32_MAX / 4;  // blocks count as int32
     if (mixed) {
         const bool wide = h->prefill_rows == kWidePrefillRows;
-        MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), 0, h->n_decode_tiles, 0, 0, 0};
+        MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), {}};
         m.a.tiles = reinterpret_cast<const TileRec*>(pd + h->off_prefill_tiles);
-        const int64_t blocks = mixed_order(&m, int64_t(h->n_prefill_tiles) << int(wide));
+        constexpr int64_t kRound = 256;  // one per CU
+        const int64_t blocks = mixed_order(&m.order, int64_t(h->n_prefill_tiles) << int(wide), h->n_decode_tiles, kRound);
         const void* fn = h->d == 64 ? reinterpret_cast<const void*>(&attn_mixed_kernel<64, false>)
                          : wide     ? reinterpret_cast<const void*>(&attn_mixed_kernel<128, true>)
                                     : reinterpret_cast<const void*>(&attn_mixed_kernel<128, false>);
