@@ -91,7 +91,9 @@ __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirs
 // kernels order the copies themselves: s_waitcnt vmcnt and a barrier before a
 // staged buffer is read, a barrier before it is overwritten. M0 is saved and
 // restored around the copies, with the wait state the hardware needs between
-// an M0 write and its use.
+// an M0 write and its use. Nor does the compiler count wait states into the
+// block: a base it has just restored from a spill (v_readlane) is read five
+// wait states after at the earliest, so the first copy stands behind that many.
 __device__ __forceinline__ uint32_t lds_wave_base(LDS void* p) {
     return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)p);
 }
@@ -102,7 +104,7 @@ __device__ __forceinline__ void copy_page(const void* base, const uint32_t (&off
     static_assert(IPP == 2 || IPP == 4, "a page is 2 or 4 KiB");
     if constexpr (IPP == 4)
         asm volatile(
-            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 2\n\t"
             "global_load_lds_dwordx4 %2, %6\n\tglobal_load_lds_dwordx4 %3, %6 offset:1024\n\t"
             "global_load_lds_dwordx4 %4, %6 offset:2048\n\tglobal_load_lds_dwordx4 %5, %6 offset:3072\n\t"
             "s_nop 0\n\ts_mov_b32 m0, %0"
@@ -111,7 +113,7 @@ __device__ __forceinline__ void copy_page(const void* base, const uint32_t (&off
             : "memory");
     else
         asm volatile(
-            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+            "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 2\n\t"
             "global_load_lds_dwordx4 %2, %4\n\tglobal_load_lds_dwordx4 %3, %4 offset:1024\n\t"
             "s_nop 0\n\ts_mov_b32 m0, %0"
             : "=&s"(saved)
@@ -174,8 +176,10 @@ constexpr float kRescaleThreshold = 8.0f;
 
 // Split partials cross the XCDs, whose L2s are not coherent: stores write
 // through to memory and loads bypass the L2 (agent scope, sc1).
+// The 16-byte store's data registers may be written again two wait states after
+// it at the earliest, which the compiler does not see in assembly.
 __device__ __forceinline__ void store_agent(float* p, float4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
 }
 __device__ __forceinline__ void store_agent(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
