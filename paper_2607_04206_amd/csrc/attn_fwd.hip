@@ -27,14 +27,13 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <mutex>
-#include <random>
 #include <string>
 #include <type_traits>
 
 #include "../../include/sangam_attn.h"
 #include "mixed_order.h"
+#include "nonce.h"
 #include "plan_format.h"
 
 namespace sangam {
@@ -1060,23 +1059,6 @@ hipError_t launch_decode(const AttnArgs& args, int n_tiles, int qw, int kw, int 
     }
     *supported = false;
     return hipSuccess;
-}
-
-// A number no other call and no leftover memory holds: a mixed counter that
-// starts at a random place in each process; never 0.
-uint64_t next_nonce() {
-    static const uint64_t seed = [] {
-        std::random_device rd;
-        return uint64_t(rd()) << 32 | rd();
-    }();
-    static std::atomic<uint64_t> calls{0};
-    for (;;) {
-        uint64_t x = seed + calls.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
-        x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;  // splitmix64 (Steele, Lea, Flood, 2014), a bijection
-        x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-        x ^= x >> 31;
-        if (x) return x;
-    }
 }
 
 sangam_status hip_fail(hipError_t e, const char* what) {
