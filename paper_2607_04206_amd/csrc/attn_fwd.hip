@@ -1208,8 +1208,7 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
                   h->mark_bytes > 0 ? next_nonce() : 0};
     // 1. attention: prefill-shaped tiles (compute-bound) first, then
     // decode-shaped tiles; both also write the fresh rows into their pages
-    const bool mixed = h->n_prefill_tiles > 0 && h->n_decode_tiles > 0 && h->decode_qw == 1 && h->decode_kw == 2 &&
-                       int64_t(h->n_prefill_tiles) + h->n_decode_tiles < INT32_MAX / 4;  // blocks count as int32
+    const bool mixed = one_launch(*h);
     if (mixed) {
         const bool wide = h->prefill_rows == kWidePrefillRows;
         MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), {}};

@@ -123,6 +123,16 @@ struct PlanHeader {
     uint64_t off_page_info;  // uint32 per page (page_indptr order), when any item is kItemPosList
 };
 
+// Whether one launch holds the prefill-shaped tiles and the block decodes
+// (attn_mixed_kernel): the shapes it has code for, and blocks that count as
+// int32. Other plans take a launch for each kind, which refuse the shapes that
+// they have no kernel for.
+inline bool one_launch(const PlanHeader& h) {
+    return h.n_prefill_tiles > 0 && h.n_decode_tiles > 0 && h.decode_qw == 1 && h.decode_kw == 2 && h.decode_nb == 1 &&
+           (h.prefill_rows == kPrefillRows || (h.prefill_rows == kWidePrefillRows && h.d == 128)) &&
+           int64_t(h.n_prefill_tiles) + h.n_decode_tiles < INT32_MAX / 4;
+}
+
 // Split partials that the allocation-free forward holds.
 constexpr size_t kScratchBytes = size_t(32) << 20;
 
