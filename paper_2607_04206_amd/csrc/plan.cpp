@@ -261,7 +261,8 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
     chunk = std::min<int64_t>(std::max<int64_t>(round_up(std::max<int64_t>(chunk, 1), kKeyAlign),
                                                 underfilled ? min_chunk_idle(qw) : min_chunk(qw)),
                               kForcedSplitLen);
-    if (underfilled) {
+    // (forced splits and block decodes in prefill-shaped tiles do not read it)
+    if (underfilled && !fuse && d->force_kv_splits == 0) {
         // Cutting further than the work-groups the chip keeps resident (two
         // MHA or one GQA whole-group work-group per CU) only adds merge work
         // and per-tile start-up: the chunk is the shortest (from the floor
