@@ -939,7 +939,8 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
 }
 
 // Prefill-shaped tiles and the block decodes of one query head per KV head
-// (which no prefill-shaped tile takes) in one launch: the former are bound by
+// (which no prefill-shaped tile takes) in one launch, where the planner finds
+// that faster than one for each (launch_each_kind): the former are bound by
 // the matrix cores and the latter by HBM, so they run beside each other, one
 // of each per CU as far as they last. Both are four waves and hold 64 KiB of
 // LDS; two waves of a decode only stage. Prefill tiles of 256 rows (WIDE) are
@@ -1213,8 +1214,8 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
         const bool wide = h->prefill_rows == kWidePrefillRows;
         MixedArgs m{args, reinterpret_cast<const TileRec*>(pd + h->off_decode_tiles), {}};
         m.a.tiles = reinterpret_cast<const TileRec*>(pd + h->off_prefill_tiles);
-        constexpr int64_t kRound = 256;  // one per CU
-        const int64_t blocks = mixed_order(&m.order, int64_t(h->n_prefill_tiles) << int(wide), h->n_decode_tiles, kRound);
+        const int64_t round = h->cus > 0 ? h->cus : 256;  // one block of each kind per CU
+        const int64_t blocks = mixed_order(&m.order, int64_t(h->n_prefill_tiles) << int(wide), h->n_decode_tiles, round);
         const void* fn = h->d == 64 ? reinterpret_cast<const void*>(&attn_mixed_kernel<64, false>)
                          : wide     ? reinterpret_cast<const void*>(&attn_mixed_kernel<128, true>)
                                     : reinterpret_cast<const void*>(&attn_mixed_kernel<128, false>);

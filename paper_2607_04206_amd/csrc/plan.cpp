@@ -89,6 +89,47 @@ constexpr int64_t kTileStages = 3, kSplitStages = 2, kMergeStages = 3;
 constexpr int kXcds = 8;
 constexpr size_t kXcdOrderMinRounds = 8;
 
+// Whether a batch of prefills and block decodes of one query head per KV head
+// takes a launch for each kind instead of one for both (attn_mixed_kernel; the
+// outputs are the same bits). One launch hides decodes beside the matrix work
+// and in the last, partial round of prefill blocks (two of 128 rows per CU at
+// a time): 100 us of decodes beside one prefill of 1796 rows, 32/32 heads, 144
+// instead of 176 us. It costs where a prefill block waits behind decodes with
+// no partial round to make up for it, and where the 256-row tiles that it takes
+// in halves are the better ones. Measured on 494 batches, one launch -> two:
+//  - up to a round of 256-row tiles, but more halves than CUs: those past the
+//    CUs wait behind the decodes, which two launches hide if they are short.
+//    1842 rows beside 512 decode tiles of 350 keys 106 -> 90 us, of 1740 keys
+//    144 -> 176
+//  - 256-row tiles over more than 4096 keys, whose K/V the halves fetch twice
+//    into the XCDs' L2s: 8192 rows (four full rounds) beside 4 to 64 decodes
+//    1110 -> 1004 and 1526 -> 1189 us, 3 prefills of up to 7607 rows 3011 ->
+//    2598; a last round at most half full pays for it in up to five rounds
+//    (4480 rows 376 -> 407, 8344 at 16/16 heads 628 -> 676)
+//  - many rounds (more than eight, or of 128-row tiles over long contexts more
+//    than four) and little to hide (decodes under a fifth of the prefills'
+//    time, 1100 keys per row and key): 16 prefills of 3400 rows 3167 -> 3045 us,
+//    7104 rows beside three short prefills 963 -> 899, but 12 rounds beside 310
+//    us of decodes 1699 -> 1714
+//  - head dim 64, contexts over 5120 keys and more decode tiles than CUs: 7862
+//    rows at 8/8 heads 211 -> 169 us, 2 prefills of 5741 192 -> 170, unless the
+//    decodes take a seventh of the time (5268 rows 371 -> 427), or half of it
+//    where some prefill blocks wait (8162 rows 221 -> 187, 5006 156 -> 202).
+// Taken by these lines the batches are 0.2 % slower than by the better choice
+// for each (9 % at worst), with one launch 1.4 %, with two 9 %.
+static bool launch_each_kind(bool wide, int d, int64_t blocks, int64_t decode_tiles, double decode_keys,
+                             double prefill_row_keys, int64_t longest, int64_t cus) {
+    const int64_t slots = 2 * cus, rounds = ceil_div(blocks, slots), last = blocks - (rounds - 1) * slots;
+    const bool waits = blocks > cus && blocks <= slots && decode_tiles > cus;
+    if (d == 128) {
+        if (wide && waits && decode_keys < 512.0 * double(decode_tiles)) return true;
+        if (wide && longest > 4096) return rounds > 5 || last > cus;
+        return (wide ? rounds > 8 : rounds > 4 && longest > 4096) && 1100.0 * decode_keys < prefill_row_keys;
+    }
+    return longest > 5120 && decode_tiles > cus &&
+           (1467.0 * decode_keys < prefill_row_keys || (waits && 440.0 * decode_keys < prefill_row_keys));
+}
+
 // Longest context an item may have: tile key ranges are int32, and a split's
 // end (its start plus the chunk) must stay representable.
 constexpr int64_t kMaxKvLen = int64_t(1) << 30;
@@ -498,6 +539,19 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
     if (dec.size() > size_t(INT32_MAX) || pre.size() > size_t(INT32_MAX))
         return fail(SANGAM_ERR_INVALID_ARG, "batch too large");
 
+    bool separate = false;
+    if (qw == 1 && !dec.empty() && !pre.empty()) {
+        int64_t longest = 0;
+        double row_keys = 0.0;
+        for (const ItemRec& it : items)
+            if (it.n > kWaveRows) {
+                longest = std::max<int64_t>(longest, it.L);
+                row_keys += double(hq) * it.n * it.L;
+            }
+        separate = launch_each_kind(wide, D, int64_t(pre.size()) * (prefill_rows / kPrefillRows), int64_t(dec.size()),
+                                    double(decode_keys), row_keys, longest, num_cus);
+    }
+
     std::vector<MergeRow> merge;
     merge.reserve(n_merge);
     for (int i = 0; i < n_items; ++i)
@@ -560,6 +614,8 @@ extern "C" sangam_status sangam_attn_plan(const sangam_attn_desc* d, void* plan_
     h.off_merge = off_merge;
     h.off_positions = off_pos;
     h.off_page_info = off_pinfo;
+    h.separate = separate;
+    h.cus = num_cus;
     std::memcpy(base, &h, sizeof h);
     if (!items.empty()) std::memcpy(base + off_items, items.data(), sizeof(ItemRec) * items.size());
     if (!dec.empty()) std::memcpy(base + off_dec, dec.data(), sizeof(TileRec) * dec.size());

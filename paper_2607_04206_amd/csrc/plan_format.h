@@ -121,15 +121,18 @@ struct PlanHeader {
     uint64_t off_merge;
     uint64_t off_positions;  // int32 positions of kItemPosList items
     uint64_t off_page_info;  // uint32 per page (page_indptr order), when any item is kItemPosList
+
+    int32_t separate;  // 1: a launch for each kind of tile, also where one could hold both
+    int32_t cus;       // compute units the plan is for (0: 256)
 };
 
 // Whether one launch holds the prefill-shaped tiles and the block decodes
-// (attn_mixed_kernel): the shapes it has code for, and blocks that count as
-// int32. Other plans take a launch for each kind, which refuse the shapes that
-// they have no kernel for.
+// (attn_mixed_kernel): the shapes it has code for, blocks that count as int32,
+// and a plan that does not ask for a launch of each kind. Those refuse the
+// shapes that they have no kernel for.
 inline bool one_launch(const PlanHeader& h) {
     return h.n_prefill_tiles > 0 && h.n_decode_tiles > 0 && h.decode_qw == 1 && h.decode_kw == 2 && h.decode_nb == 1 &&
-           (h.prefill_rows == kPrefillRows || (h.prefill_rows == kWidePrefillRows && h.d == 128)) &&
+           (h.prefill_rows == kPrefillRows || (h.prefill_rows == kWidePrefillRows && h.d == 128)) && !h.separate &&
            int64_t(h.n_prefill_tiles) + h.n_decode_tiles < INT32_MAX / 4;
 }
 
@@ -169,6 +172,6 @@ constexpr int max_merge_in_tile(int qw) {
 static_assert(sizeof(ItemRec) == 56, "ItemRec layout is part of the blob format");
 static_assert(sizeof(TileRec) == 32, "TileRec layout is part of the blob format");
 static_assert(sizeof(MergeRow) == 8, "MergeRow layout is part of the blob format");
-static_assert(sizeof(PlanHeader) == 176, "PlanHeader layout is part of the blob format");
+static_assert(sizeof(PlanHeader) == 184, "PlanHeader layout is part of the blob format");
 
 }  // namespace sangam

@@ -26,5 +26,5 @@ def test_no_search_whose_chunk_is_not_read(prefills, kw):
     small, p = best_of(15, wl, num_cus=256, **kw)
     large, q = best_of(15, wl, num_cus=1 << 24, **kw)
     if prefills:  # (forced splits of decodes alone take other tiles on a chip that they would not fill)
-        assert p.info.num_fused_decode_tiles == 40 * 4 * 2 and np.array_equal(p.host, q.host)
+        assert p.info.num_fused_decode_tiles == 40 * 4 * 2 and np.array_equal(p.host[256:], q.host[256:])  # the headers state the CUs
     assert large < 5 * small + 1e-3, (small, large)
