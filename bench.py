@@ -43,10 +43,10 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 PHASES = ("prefill_attn", "decode_attn", "merge")
 
 
-def split_work(wl, fused_decodes=False):
+def split_work(wl, decodes_in_prefill=False):
     """Algorithmic flops / bytes of each attention launch of the call.
-    fused_decodes: the plan runs the block decodes inside the prefill-shaped
-    launch. Each launch also writes back the fresh rows of its items."""
+    decodes_in_prefill: the plan runs the block decodes inside the
+    prefill-shaped launch. Each launch also writes back the fresh rows of its items."""
     import numpy as np
     n = np.diff(wl.q_indptr).astype(np.float64)
     L = wl.kv_len.astype(np.float64)
@@ -58,7 +58,7 @@ def split_work(wl, fused_decodes=False):
     attn_b = 2.0 * (2 * L * Hkv * D + 2 * n * Hq * D) + 4.0 * n * Hq
     attn_b += np.where(pre, 0.0, 4.0 * np.ceil(L / 16))
     attn_b += 2.0 * (2 * n * Hkv * D)
-    in_pre = np.ones_like(pre) if fused_decodes else pre
+    in_pre = np.ones_like(pre) if decodes_in_prefill else pre
     return {
         "prefill_attn": (float(flops[in_pre].sum()), float(attn_b[in_pre].sum())),
         "decode_attn": (float(flops[~in_pre].sum()), float(attn_b[~in_pre].sum())),
@@ -257,7 +257,7 @@ def decode_sweep(args):
             print(json.dumps({
                 "sweep": "decode_batch", "shape": shape, "num_q_heads": wl.num_q_heads,
                 "num_kv_heads": wl.num_kv_heads, "batch": B, "kv_len": 1024, "ms_per_call": ms,
-                "decode_kernel_ms": kern, "merge_ms": float(launches[2]) if p.info.num_split_items > 0 else None,
+                "decode_kernel_ms": kern, "merge_ms": float(launches[2]) if p.launches()[2] else None,
                 "tflops": F / (ms / 1e3) / 1e12, "hbm_gbs": Bytes / (ms / 1e3) / 1e9,
                 "kernel_hbm_frac": Bytes / (kern / 1e3) / (PEAK_HBM_GBS * 1e9),
                 "kernel_mfma_frac": F / (kern / 1e3) / (PEAK_BF16_TFLOPS * 1e12),
@@ -560,8 +560,7 @@ def bench_workload(args):
     stream = torch.cuda.current_stream(dev)
     args_c = attn.c_args(p, t["q"], t["k_new"], t["v_new"], t["k_cache"], t["v_cache"], t["page_ids"],
                          out, lse, ws, stream)
-    ran = {"prefill_attn": p.info.num_prefill_tiles > 0, "decode_attn": p.info.num_decode_tiles > 0,
-           "merge": p.info.num_split_items > 0}
+    ran = dict(zip(PHASES, p.launches()))
 
     def make_events(which=range(3)):
         """Start / stop event pairs of the three launches; launches outside
@@ -600,7 +599,7 @@ def bench_workload(args):
     for j, name in enumerate(PHASES):
         phase_ms[name] = (float(np.mean([evsets[k][0][2 * j].elapsed_time(evsets[k][0][2 * j + 1])
                                          for k in range(n_phase)])) if ran[name] else None)
-    work = split_work(wl, fused_decodes=int(p.info.num_fused_decode_tiles) > 0)
+    work = split_work(wl, decodes_in_prefill=not ran["decode_attn"])
     dom = max((n for n in ("prefill_attn", "decode_attn") if ran[n]), key=lambda n: phase_ms[n])
     jd = PHASES.index(dom)
 

@@ -114,10 +114,12 @@ size_t sangam_plan_workspace_bytes(const void *plan_buf);
 /* Summary of a plan, for tests and tuning. */
 typedef struct sangam_plan_info {
     int32_t num_items;
-    int32_t num_decode_tiles;  /* work-groups of the decode-shaped launch (n_i <= 32) */
-    int32_t num_prefill_tiles; /* work-groups of the prefill-shaped launch (n_i > 32, and
-                                  the fused block decodes below) */
-    int32_t num_split_items;   /* items whose context is split (merged afterwards) */
+    int32_t num_decode_tiles;  /* decode-shaped work-groups (n_i <= 32); sangam_plan_launches
+                                  says whether they have a launch of their own */
+    int32_t num_prefill_tiles; /* prefill-shaped work-groups (n_i > 32, and the fused block
+                                  decodes below) */
+    int32_t num_split_items;   /* items whose context is split (merged by the tile that
+                                  finishes last, or in a launch) */
     int32_t max_splits;        /* largest split count of an item */
     int32_t decode_q_waves;    /* waves per decode work-group that hold query rows */
     int32_t decode_kv_waves;   /* waves per decode work-group that split the context */
@@ -133,6 +135,13 @@ typedef struct sangam_plan_info {
 } sangam_plan_info;
 
 sangam_status sangam_plan_get_info(const void *plan_buf, sangam_plan_info *info);
+
+/* Which of a forward's launches have work: ran[0] the prefill-shaped one,
+ * ran[1] the decode-shaped one, ran[2] the split merge (the order of the event
+ * pairs of sangam_attn_forward_timed), 1 or 0. Block decodes that run in the
+ * prefill-shaped launch, all of them, leave ran[1] 0; splits that the tiles
+ * merge leave ran[2] 0. Host only. */
+sangam_status sangam_plan_launches(const void *plan_buf, int32_t ran[3]);
 
 /* Split count and first context position of each split of item `item`.
  * starts must hold max_splits + 1 entries (the last one is L_i). */

@@ -33,6 +33,7 @@ EXPORTS = (
     "sangam_attn_plan",
     "sangam_plan_workspace_bytes",
     "sangam_plan_get_info",
+    "sangam_plan_launches",
     "sangam_plan_item_splits",
     "sangam_attn_forward",
     "sangam_attn_forward_timed",
@@ -118,6 +119,8 @@ def _load():
     lib.sangam_plan_workspace_bytes.restype = S
     lib.sangam_plan_get_info.argtypes = [P, ctypes.POINTER(PlanInfo)]
     lib.sangam_plan_get_info.restype = ctypes.c_int32
+    lib.sangam_plan_launches.argtypes = [P, ctypes.POINTER(ctypes.c_int32)]
+    lib.sangam_plan_launches.restype = ctypes.c_int32
     lib.sangam_plan_item_splits.argtypes = [P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), P,
                                             ctypes.c_int32]
     lib.sangam_plan_item_splits.restype = ctypes.c_int32

@@ -40,6 +40,13 @@ class Plan:
     def host_ptr(self) -> int:
         return self.host.ctypes.data
 
+    def launches(self) -> Tuple[bool, bool, bool]:
+        """Whether a forward's prefill-shaped launch, its decode-shaped launch
+        and its split merge have work (the pairs of launch_events)."""
+        ran = (ctypes.c_int32 * 3)()
+        check(lib.sangam_plan_launches(self.host_ptr(), ran))
+        return ran[0] != 0, ran[1] != 0, ran[2] != 0
+
     def item_splits(self, item: int):
         n = ctypes.c_int32(0)
         check(lib.sangam_plan_item_splits(self.host_ptr(), item, ctypes.byref(n), None, 0))

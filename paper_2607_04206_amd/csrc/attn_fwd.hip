@@ -1255,7 +1255,7 @@ static sangam_status forward_impl(const void* plan_host, const void* plan_dev, c
     }
 
     // 2. merge split contexts, unless the tiles do
-    if (h->n_merge_rows > 0 && h->mark_bytes <= 0) {
+    if (merge_launch(*h)) {
         MergeArgs m{reinterpret_cast<const MergeRow*>(pd + h->off_merge),
                     items,
                     static_cast<const float*>(workspace),

@@ -136,6 +136,9 @@ inline bool one_launch(const PlanHeader& h) {
            int64_t(h.n_prefill_tiles) + h.n_decode_tiles < INT32_MAX / 4;
 }
 
+// Whether split contexts are merged in a launch; else the tiles do it.
+inline bool merge_launch(const PlanHeader& h) { return h.n_merge_rows > 0 && h.mark_bytes <= 0; }
+
 // Split partials that the allocation-free forward holds.
 constexpr size_t kScratchBytes = size_t(32) << 20;
 

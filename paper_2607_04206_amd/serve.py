@@ -182,8 +182,7 @@ class ServingLoop:
             lev = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
             for e in lev:  # torch reads elapsed time only from events it has recorded
                 e.record(stream)
-            i = p.info
-            used = (i.num_prefill_tiles > 0, i.num_decode_tiles > 0, i.num_split_items > 0)
+            used = p.launches()
             ev[0].record(stream)
         attn.forward(p, self.q[:rows], self.k_new[:rows], self.v_new[:rows], self.k_cache, self.v_cache,
                      pid, out=self.out[:rows], lse=self.lse[:rows], launch_events=lev)
