@@ -1,9 +1,10 @@
-"""Wait states that the compiler does not put into inline assembly, checked in
-the instructions of the built library: an SGPR written by the VALU (a spilled
-base comes back by v_readlane) is read by a memory instruction at the earliest
-five wait states later, and the data registers of a 16-byte store are written
-again at the earliest two after it. The assembly blocks hold them themselves,
-whatever the compiler puts around them. CPU only."""
+"""Wait states in the instructions of the built library. Those that the compiler
+does not put into inline assembly: an SGPR written by the VALU (a spilled base
+comes back by v_readlane) is read by a memory instruction at the earliest five
+wait states later, and the data registers of a 16-byte store are written again
+at the earliest two after it; the assembly blocks hold them themselves, whatever
+the compiler puts around them. And those between an MFMA and the use of its
+result. CPU only."""
 import os
 import re
 import shutil
