@@ -181,7 +181,7 @@ def cpu_baseline(wl, budget_s, single_thread=True):
 def kernel_source_hash():
     import hashlib
     h = hashlib.sha256()
-    for f in ("attn_fwd.hip", "plan.cpp", "plan_format.h"):
+    for f in ("attn_fwd.hip", "mixed_order.h", "plan.cpp", "plan_format.h"):
         with open(os.path.join(ROOT, "paper_2607_04206_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -175,10 +175,10 @@ sangam_status sangam_attn_forward(const void *plan_host, const void *plan_dev, c
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * call as sangam_attn_forward, with the split-KV partial results in a
  * library-owned device array instead of a caller workspace. It calls no
- * allocator. The array holds sangam_noalloc_scratch_bytes() bytes (32 MiB)
- * per GPU; each GPU the library runs on keeps its own copy until the process
- * ends. Its address is looked up once per device, on the first call with
- * that device current. `stream` must belong to the current device.
+ * allocator. The array holds sangam_noalloc_scratch_bytes() bytes (32 MiB) of
+ * partials and a third as many for their marks (42.7 MiB in all) per GPU; each
+ * GPU the library runs on keeps its own copy until the process ends. Its address
+ * is looked up once per device, on the first call with that device current. `stream` must belong to the current device.
  * Every call on one GPU shares that GPU's array: two calls that overlap in
  * time on one GPU (different streams, or threads) race on it; serialize
  * them. The array keeps the last call's contents; nothing in it needs to
@@ -194,8 +194,8 @@ sangam_status sangam_attn_forward_noalloc(const void *plan_host, const void *pla
                                           const int32_t *page_ids_dev, int64_t num_page_ids,
                                           void *out, float *lse, void *stream);
 
-/* Bytes of the device array that sangam_attn_forward_noalloc uses for split
- * partials (a plan whose workspace is no larger always fits). */
+/* Bytes of split partials that sangam_attn_forward_noalloc's device array holds
+ * (a plan whose workspace is no larger always fits). */
 size_t sangam_noalloc_scratch_bytes(void);
 
 /*

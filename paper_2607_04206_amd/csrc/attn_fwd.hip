@@ -23,7 +23,10 @@
 //                     into XOR-swizzled tiles (double buffered); V^T operands
 //                     come from ds_read_b64_tr_b16 transposing reads. Output
 //                     rows leave through LDS, whole rows per 16 lanes.
-//   merge_kernel      combines split-context partial (O, LSE) in split order.
+//   attn_mixed_kernel the same tiles, prefill-shaped ones and block decodes of
+//                     one query head per KV head in one launch.
+//   merge_kernel      combines split-context partial (O, LSE) in split order,
+//                     in calls whose tiles do not do so themselves.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -233,7 +236,8 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     // Two waves share a SIMD. Measured: 128-key stages QK^T (long prefills
     // 6,510 us with PV, 6,480 with it), 64-key ones PV (Dream mixed batch 261
     // us with QK^T or none, 255 with it), D = 64 none (mixed batch 80.9 us
-    // with PV, 76.4 without).
+    // with PV, 76.4 without). Decode batches take the same time either way
+    // (1 to 48 decodes, 14.8 to 78 us, within 0.2 %).
     constexpr int PRIO = D == 64 ? 0 : NB == 4 ? 1 : 2;
     constexpr int RA = 4;                // steps between a fragment's LDS read and its MFMA
     constexpr int MERGE_REGS = MB * 16 + 2;
@@ -947,12 +951,13 @@ __global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_k
 // taken as two of 128 that keep their 128-key stages, so that a prefill's sums
 // are those of a launch without decodes, bit for bit: K and V have one buffer
 // each and take turns (with two of 64 keys each, 16 decodes beside 1819 and
-// 1201 rows take 175 us instead of 180, but the sums differ by 2e-3).
+// 1201 rows, 32/32 heads, take 195 us instead of 199, but the sums differ by
+// 2e-3).
 // Order: `round` prefill tiles (one per CU), as many decodes, then groups of
 // eight blocks (one per XCD) of either kind in the ratio of what is left.
-// Measured on 16 block decodes beside prefills of 1819 and 1201 rows, 32/32
-// heads: 229 us in two launches (110 + 118), 194 us in this one; all prefill
-// tiles first 206, all decodes first 212, no first round 197.
+// Measured on the same batch: 231 us in two launches, 198 in this one (the order
+// was taken with the 64-key halves: 194 us, all prefill tiles first 206, all
+// decodes first 212, no first round 197).
 struct MixedArgs {
     AttnArgs a;                   // tiles: the prefill-shaped ones
     const TileRec* decode_tiles;
