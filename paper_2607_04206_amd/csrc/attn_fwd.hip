@@ -191,9 +191,18 @@ __device__ __forceinline__ float load_agent(const float* p) {
 }
 constexpr int kBufferAgent = 16;  // sc1 in a buffer load's cache policy
 
+// Decode tiles of five to eight query heads at head dim 64 fit twice or three
+// times on a CU with 128 registers a wave (four waves per SIMD), once or twice
+// with the 165 they take otherwise. They get there with fragments read two steps
+// ahead instead of four and with no more splits' sums than they merge. Measured
+// with 165 -> 128 registers: 100 decodes of 1500 keys, 28/4 heads, 67.5 -> 61.2
+// us, 150 of 20/4 95.0 -> 75.1, 250 of 64/8 304 -> 276; launches of up to one
+// work-group per CU take the same time.
+constexpr bool few_registers(int d, int qw, bool heads_across) { return d == 64 && heads_across && qw >= 5; }
+
 // Waves per SIMD the register budget is sized for: two (256 registers) when a
 // wave holds one query block.
-constexpr int waves_per_simd(int qb) { return qb == 1 ? 2 : 1; }
+constexpr int waves_per_simd(int qb, bool few) { return few ? 4 : qb == 1 ? 2 : 1; }
 
 // LDS of a work-group
 template <int BYTES>
@@ -239,7 +248,9 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
     // with PV, 76.4 without). Decode batches take the same time either way
     // (1 to 48 decodes, 14.8 to 78 us, within 0.2 %).
     constexpr int PRIO = D == 64 ? 0 : NB == 4 ? 1 : 2;
-    constexpr int RA = 4;                // steps between a fragment's LDS read and its MFMA
+    constexpr bool FEW = few_registers(D, QW, HEADS_ACROSS);
+    constexpr int RA = FEW ? 2 : 4;      // steps between a fragment's LDS read and its MFMA
+    constexpr int MAXS = FEW ? max_merge_in_tile(QW) : kMaxMergeInTile;  // splits that a tile merges
     constexpr int MERGE_REGS = MB * 16 + 2;
     static_assert(KW == 1 || QB == 1, "context-splitting waves hold one query block");
     static_assert(!HEADS_ACROSS || QB == 1, "a decode block is 32 rows");
@@ -844,12 +855,12 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
             const int row = min(qn, nb - 1);  // lanes past the last row repeat it
             const size_t step = (size_t)a.hq * it.n;  // rows between splits
             const size_t first = (size_t)head * it.n + r0;
-            float ls[kMaxMergeInTile], mx = -INFINITY;
+            float ls[MAXS], mx = -INFINITY;
 #pragma unroll
-            for (int k = 0; k < kMaxMergeInTile; ++k)
+            for (int k = 0; k < MAXS; ++k)
                 if (k < it.num_splits) ls[k] = load_agent(a.ws + it.ws_lse + k * step + first + row);
 #pragma unroll
-            for (int k = 0; k < kMaxMergeInTile; ++k)
+            for (int k = 0; k < MAXS; ++k)
                 if (k < it.num_splits) mx = fmaxf(mx, ls[k]);
             f32x16 acc[MBW];
             float tot = 0.0f;
@@ -869,7 +880,7 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
                 }
                 float w = 0.0f;
 #pragma unroll
-                for (int m = 0; m < kMaxMergeInTile; ++m)
+                for (int m = 0; m < MAXS; ++m)
                     if (m == k) w = __expf(ls[m] - mx);
                 tot += w;
 #pragma unroll
@@ -936,7 +947,7 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& a, const TileRec t, co
 }
 
 template <int D, int QW, int KW, int QB, int NB, int NSTAGE, bool HEADS_ACROSS>
-__global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB)) void attn_tiles_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * QW * KW, waves_per_simd(QB, few_registers(D, QW, HEADS_ACROSS))) void attn_tiles_kernel(AttnArgs a) {
     __shared__ TileShared<2 * NSTAGE * 32 * NB * KW * D * 2> shared;
     const TileRec t = a.tiles[blockIdx.x];
     attn_tile<D, QW, KW, QB, NB, NSTAGE, HEADS_ACROSS, 0>(a, t, a.items[t.item], shared);
